@@ -58,9 +58,13 @@ Sizes sizes_of(const envpic_params& p) {
   // enter a moving window, and the columns injected until the layout is
   // rebuilt
   const long long column = (long long)p.nr * s.ppc;
+  // (and the padding of the aligned segments, where the slot limit leaves
+  // room for it)
   s.capacity = p.capacity > 0 ? p.capacity
                               : window + window / 4 + (long long)(ENTERING_TILES + 1) * TX * column +
                                     (SORT_EVERY * (CELL_SORT_EVERY + 1LL) + 1) * column + 1024;
+  const long long padding = (long long)s.ntiles * SLOT_ALIGN;
+  if (p.capacity == 0 && s.capacity + padding < (1LL << 30)) s.capacity += padding;
   // work-item size: about four items per compute unit (256 of them) so that
   // small runs fill the device, at most CHUNK (CHUNK / 2 with quadratic
   // shapes, whose particles cost more than the staging and flush of an
@@ -561,18 +565,25 @@ template <class R> struct SimT : envpic_sim {
   }
   int launched(const char* what) { return hip_check(hipGetLastError(), what); }
 
-  // host-built layout of a particle set sorted by tile key: offsets per key
-  // and work items of <= chunk particles
-  int upload_layout(int b, const std::vector<int>& counts) {
+  // first slot of each tile's segment for these counts (and the end of the
+  // last): aligned while the columns injected before the layout is rebuilt
+  // still fit, packed otherwise
+  std::vector<int> segment_offsets(const std::vector<int>& counts) const {
     std::vector<int> off(sz.ntiles + 1, 0);
+    long long end = 0;
+    for (int t = 0; t < sz.ntiles; ++t) end += round_slots(counts[t], SLOT_ALIGN);
+    const int align = end + slot_reserve(p, sz) <= sz.capacity ? SLOT_ALIGN : 1;
+    for (int t = 0; t < sz.ntiles; ++t) off[t + 1] = off[t] + round_slots(counts[t], align);
+    return off;
+  }
+  // host-built layout of a particle set sorted by tile key: work items of <=
+  // chunk particles over the segments from `off`
+  int upload_layout(int b, const std::vector<int>& counts, const std::vector<int>& off) {
     std::vector<int4> items;
     for (int t = 0; t < sz.ntiles; ++t) {
-      off[t + 1] = off[t] + counts[t];
-      const int nm = (counts[t] + sz.chunk - 1) / sz.chunk;  // equal shares, as in the device scan
-      for (int k = 0; k < nm; ++k) {
-        const int lo = (int)((long long)k * counts[t] / nm), hi = (int)((long long)(k + 1) * counts[t] / nm);
-        items.push_back(make_int4(t, off[t] + lo, hi - lo, 0));
-      }
+      const int sh = item_share(counts[t], sz.chunk);  // as in the device scan
+      for (int lo = 0; lo < counts[t]; lo += sh)
+        items.push_back(make_int4(t, off[t] + lo, std::min(sh, counts[t] - lo), 0));
     }
     if ((int)items.size() > sz.max_items - sz.ntr) return fail(ENVPIC_ENOMEM, "work-item list overflow");
     const int ni = (int)items.size();
@@ -608,7 +619,7 @@ template <class R> struct SimT : envpic_sim {
           counts[(T % sz.ntxa) * sz.ntr + tr] = cols * rows * sz.ppc;
         }
     lay = cur;
-    if ((rc = upload_layout(lay, counts))) return rc;
+    if ((rc = upload_layout(lay, counts, segment_offsets(counts)))) return rc;
     if (p.profile != ENVPIC_PROFILE_NONE) launch_init_particles<R>(g, plasma(), S.parts[cur], S.lay[lay].offsets, stream);
     launch_init_envelope<R>(g, S.grids, laser(), fp64_rows ? 1 : 0, stream);
     if ((rc = launched("init kernels"))) return rc;
@@ -1004,13 +1015,13 @@ template <class R> struct SimT : envpic_sim {
       key[k] = tile_key(g, ixv[k], jr);
       counts[key[k]]++;
     }
-    std::vector<int> off(sz.ntiles + 1, 0);
-    for (int t = 0; t < sz.ntiles; ++t) off[t + 1] = off[t] + counts[t];
+    const std::vector<int> off = segment_offsets(counts);
     std::vector<int> pos(off.begin(), off.end() - 1);
-    std::vector<unsigned> hcell(np);
+    const size_t ns = (size_t)off[sz.ntiles];  // slots, the segments' padding included
+    std::vector<unsigned> hcell(ns, kDead);
     std::vector<R> h[7];
-    for (int c = 0; c < 7; ++c) h[c].resize(np);
-    std::vector<uint32_t> hid(np);
+    for (int c = 0; c < 7; ++c) h[c].resize(ns);
+    std::vector<uint32_t> hid(ns);
     for (int64_t k = 0; k < np; ++k) {
       const int d = pos[key[k]]++;
       int ix = ixv[k], jr = jrv[k];
@@ -1027,14 +1038,14 @@ template <class R> struct SimT : envpic_sim {
     }
     int rc;
     lay = cur;
-    if ((rc = upload_layout(lay, counts))) return rc;
+    if ((rc = upload_layout(lay, counts, off))) return rc;
     Parts<R>& P = S.parts[cur];
     R* dst[7] = {P.fx, P.fr, P.th, P.px, P.py, P.pz, P.w};
     if (np) {
-      if ((rc = hip_check(hipMemcpyAsync(P.cell, hcell.data(), np * sizeof(unsigned), hipMemcpyHostToDevice, stream), "cell"))) return rc;
+      if ((rc = hip_check(hipMemcpyAsync(P.cell, hcell.data(), ns * sizeof(unsigned), hipMemcpyHostToDevice, stream), "cell"))) return rc;
       for (int c = 0; c < 7; ++c)
-        if ((rc = hip_check(hipMemcpyAsync(dst[c], h[c].data(), np * sizeof(R), hipMemcpyHostToDevice, stream), "parts"))) return rc;
-      if ((rc = hip_check(hipMemcpyAsync(P.id, hid.data(), np * sizeof(uint32_t), hipMemcpyHostToDevice, stream), "id"))) return rc;
+        if ((rc = hip_check(hipMemcpyAsync(dst[c], h[c].data(), ns * sizeof(R), hipMemcpyHostToDevice, stream), "parts"))) return rc;
+      if ((rc = hip_check(hipMemcpyAsync(P.id, hid.data(), ns * sizeof(uint32_t), hipMemcpyHostToDevice, stream), "id"))) return rc;
     }
     sorted_at = n;  // the particles of P[cur] sit in their tiles
     return hip_check(hipStreamSynchronize(stream), "set_particles");

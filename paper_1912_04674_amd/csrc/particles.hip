@@ -328,11 +328,11 @@ __device__ inline int transpose_rank(int r, int R) {
 }
 
 // slot of the r-th particle (in cell order) of a tile of v particles: the
-// tile splits into nm = ceil(v / chunk) equal work items (as the scan makes
-// them), and inside an item the particles are placed as at loading.  With
+// tile splits into nm = ceil(v / chunk) work items of item_share particles
+// (as the scan makes them), and inside an item the particles are placed as at loading.  With
 // linear shapes (O = 1) an item takes a contiguous range of ranks.  With
 // quadratic shapes the ranks are dealt to the items in turn (listed by
-// r mod nm, then r / nm, and cut into the items' sizes), so that every item
+// r mod nm, then r / nm, and cut at the items' sizes), so that every item
 // spans all cells of the tile and a wavefront's lanes stay four cells apart
 // in cell order with the smaller items of that order (measured: the
 // position pass 5 % faster on the LWFA workload; with linear shapes the
@@ -346,9 +346,7 @@ template <int O> __device__ inline int placed_rank(int r, int v, int chunk) {
     const int a = v / nm, b = v - a * nm, m = r % nm;
     t = m * a + min(m, b) + r / nm;  // (the first b residues hold a + 1 ranks)
   }
-  int k = (int)((long long)t * nm / v);
-  if (k + 1 < nm && (int)((long long)(k + 1) * v / nm) <= t) ++k;
-  const int lo = (int)((long long)k * v / nm), hi = (int)((long long)(k + 1) * v / nm);
+  const int sh = item_share(v, chunk), lo = t / sh * sh, hi = min(lo + sh, v);
   return lo + transpose_rank(t - lo, hi - lo);
 }
 

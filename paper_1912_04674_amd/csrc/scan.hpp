@@ -90,13 +90,14 @@ __device__ inline void bump_pending(const Geo& g, Layout L, int* pending) {
   }
 }
 
-// Work items of v particles from slot st: ceil(v / chunk) items of equal
-// size, written from items[em] on (none past max_em); returns their number.
+// Work items of v particles from slot st: ceil(v / chunk) items of
+// item_share particles (the last holds the rest), written from items[em] on
+// (none past max_em); returns their number.
 __device__ inline int emit_items(const Geo& g, int4* items, int em, int max_em, int key, int st, int v,
                                  long long capacity) {
-  const int nm = (v + g.chunk - 1) / g.chunk;
+  const int nm = (v + g.chunk - 1) / g.chunk, sh = item_share(v, g.chunk);
   for (int k = 0; k < nm; ++k) {
-    const int lo = (int)((long long)k * v / nm), hi = (int)((long long)(k + 1) * v / nm);
+    const int lo = k * sh, hi = min(lo + sh, v);
     // items never reach past the buffer (an overflow is flagged by the caller)
     if (em + k < max_em)
       items[em + k] = ((long long)st + hi <= capacity) ? make_int4(key, st + lo, hi - lo, 0) : make_int4(key, 0, 0, 0);
@@ -109,20 +110,24 @@ __device__ inline int emit_items(const Geo& g, int4* items, int em, int max_em, 
 // (or in the one its front is in), which fill as columns are injected.
 // Other tiles get no free slots: measured on the LWFA workload, free slots of
 // 1/16 of each tile made the passes that stream the particles 5 % slower
-// (their arrivals, rare, take overflow ranges instead).
-__device__ inline int seg_room(const Geo& g, int t, int v, int entering) {
-  if (entering <= 0) return v;
-  const int tcx = t / g.ntr, tr = t - (t / g.ntr) * g.ntr;
-  const long long T = lab_tile(g, tcx), front = (g.shift + g.nx - 1) / TX;
-  if (T < front || T > front + entering) return v;
-  return max(v, TX * min(TR, g.nr - tr * TR) * g.ppc_x * g.ppc_r * g.ppc_t);
+// (their arrivals, rare, take overflow ranges instead).  `align` rounds the
+// room up, so that the next segment starts at a multiple of it.
+__device__ inline int seg_room(const Geo& g, int t, int v, int entering, int align) {
+  int room = v;
+  if (entering > 0) {
+    const int tcx = t / g.ntr, tr = t - (t / g.ntr) * g.ntr;
+    const long long T = lab_tile(g, tcx), front = (g.shift + g.nx - 1) / TX;
+    if (T >= front && T <= front + entering)
+      room = max(v, TX * min(TR, g.nr - tr * TR) * g.ppc_x * g.ppc_r * g.ppc_t);
+  }
+  return round_slots(room, align);
 }
 
 // One block of NT threads: the tile totals in hist become layout `out` of
 // the other buffer, the whole layout rebuilt: the segment of a tile of v
-// particles holds seg_room slots (the room for entering tiles only when
-// `reserve` slots past the segments stay free), and its particles form
-// ceil(v / chunk) items of equal size.  hist stays (the kernels keep it
+// particles holds seg_room slots (the room for entering tiles, and the
+// alignment of the segments, only when `reserve` slots past the segments
+// stay free), and its particles form ceil(v / chunk) items.  hist stays (the kernels keep it
 // current).  Flags when the particles plus the columns injected before the
 // next sort would not fit.
 template <int NT>
@@ -136,7 +141,7 @@ __device__ inline void full_layout(const Geo& g, int* hist, Layout out, long lon
   for (int t = t0; t < t1; ++t) {
     const int v = hist[t];
     c += v;
-    rs += seg_room(g, t, v, entering);
+    rs += seg_room(g, t, v, entering, 1);
     m += (v + g.chunk - 1) / g.chunk;
   }
   int total_c = 0, n_items = 0, total_rs = 0, seg_end = 0;
@@ -144,9 +149,19 @@ __device__ inline void full_layout(const Geo& g, int* hist, Layout out, long lon
   int em = block_scan<NT>(m, s_w, &n_items);
   block_scan<NT>(rs, s_w, &total_rs);
   const int ent = (long long)total_rs + reserve <= capacity ? entering : 0;
-  int cs = 0;
-  for (int t = t0; t < t1; ++t) cs += seg_room(g, t, hist[t], ent);
+  int cs = 0, ca = 0, aligned_end = 0;
+  for (int t = t0; t < t1; ++t) {
+    cs += seg_room(g, t, hist[t], ent, 1);
+    ca += seg_room(g, t, hist[t], ent, SLOT_ALIGN);
+  }
   int ec = block_scan<NT>(cs, s_w, &seg_end);
+  const int eca = block_scan<NT>(ca, s_w, &aligned_end);
+  int align = 1;
+  if ((long long)aligned_end + reserve <= capacity) {
+    align = SLOT_ALIGN;
+    ec = eca;
+    seg_end = aligned_end;
+  }
   // room kept for the columns injected before the next sort (one per step)
   const int item_cap = max_items - SORT_EVERY * g.ntr;
   for (int t = t0; t < t1; ++t) {
@@ -157,7 +172,7 @@ __device__ inline void full_layout(const Geo& g, int* hist, Layout out, long lon
     out.ovb[t] = 0;
     out.ovn[t] = 0;
     em += emit_items(g, out.items, em, item_cap, t, ec, v, capacity);
-    ec += seg_room(g, t, v, ent);
+    ec += seg_room(g, t, v, ent, align);
   }
   if (tid == NT - 1) {
     out.offsets[nt] = seg_end;
