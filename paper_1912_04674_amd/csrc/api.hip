@@ -527,6 +527,9 @@ template <class R> struct SimT : envpic_sim {
     g.dx = p.dx;
     g.dr = p.dr;
     g.dt = p.dt;
+    g.rdx = 1.0 / p.dx;
+    g.rdr = 1.0 / p.dr;
+    g.dtdx = p.dt / p.dx;
     g.chunk = sz.chunk;
     g.order = p.shape_order == 2 ? 2 : 1;
     // one buffer's records: cell word and id, six reals and the weight

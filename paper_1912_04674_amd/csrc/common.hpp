@@ -115,6 +115,7 @@ struct Geo {
   long long shift;   // lab column of the window's left edge
   long long cap;     // particle slots per buffer
   double dx, dr, dt;
+  double rdx, rdr, dtdx;  // 1 / dx, 1 / dr, dt / dx
   float fix;         // fixed-point scale of the FP32 path's mode-1 current sums
   double unfix;      // 1 / fix
   float fix0;        // fixed-point scale of the FP32 path's chi and mode-0 current sums

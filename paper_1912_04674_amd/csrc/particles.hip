@@ -34,10 +34,22 @@ template <class R> struct Lin {
 };
 
 template <class R> __device__ inline Lin<R> primal_w(int c, R f) { return Lin<R>{c, (R)1 - f, f}; }
+// floor as an integer and fractional part (in [0, 1): the hardware's result
+// for a tiny negative number is the largest value below 1)
+__device__ inline int floor_int(float x) {
+  int i;
+  asm("v_cvt_flr_i32_f32 %0, %1" : "=v"(i) : "v"(x));
+  return i;
+}
+__device__ inline int floor_int(double x) { return (int)floor(x); }
+__device__ inline float fract_r(float x) { return __builtin_amdgcn_fractf(x); }
+__device__ inline double fract_r(double x) { return __builtin_amdgcn_fract(x); }
+// x clamped to [lo, hi]; a NaN gives lo
+__device__ inline float clamp_r(float x, float lo, float hi) { return __builtin_amdgcn_fmed3f(x, lo, hi); }
+__device__ inline double clamp_r(double x, double lo, double hi) { return fmin(fmax(x, lo), hi); }
 template <class R> __device__ inline Lin<R> dual_w(int c, R f) {
-  R v = f - (R)0.5;
-  if (v < (R)0) return Lin<R>{c - 1, (R)0.5 - f, f + (R)0.5};
-  return Lin<R>{c, (R)1 - v, v};
+  const R v = f - (R)0.5, w = fract_r(v);
+  return Lin<R>{v < (R)0 ? c - 1 : c, (R)1 - w, w};
 }
 
 // (RL: the row length of the LDS region the values are staged in)
@@ -176,10 +188,15 @@ template <> struct Acc1<double> {
 __device__ inline unsigned long long fixed_bits(double u, double x) {
   return (unsigned long long)__double_as_longlong(fma(u, x, 6755399441055744.0));  // 1.5 * 2^52
 }
-// the sum held by a word of fixed_bits patterns: its low 48 bits, signed
-__device__ inline long long fixed_sum(long long w) {
-  return (long long)((unsigned long long)w << 16) >> 16;
+// The sum held by a word of fixed_bits patterns: its low 48 bits, signed.
+// Offset by 2^47 they become the low mantissa bits of a double in
+// [2^52, 2^53), from which the offset is subtracted (exact: two integer
+// operations on the high word and one FP64 addition).
+__device__ inline double fixed_sum(long long w) {
+  const int hi = (int)((((unsigned long long)w >> 32) & 0xFFFFu) ^ 0x8000u) | 0x43300000;
+  return __hiloint2double(hi, (int)w) - 4644337115725824.0;  // 2^52 + 2^47
 }
+__device__ inline bool fixed_nonzero(long long w) { return ((unsigned long long)w << 16) != 0; }
 template <> struct Acc1<float> {
   using T = longlong2;
   using S = long long;  // one word (real or imaginary part)
@@ -189,9 +206,9 @@ template <> struct Acc1<float> {
     atomicAdd((unsigned long long*)&a.re[k], fixed_bits(u, x));
     atomicAdd((unsigned long long*)&a.im[k], fixed_bits(u, y));
   }
-  __device__ static bool nonzero(const T& v) { return fixed_sum(v.x) != 0 || fixed_sum(v.y) != 0; }
-  __device__ static float re(const T& v, const Geo& g) { return (float)((double)fixed_sum(v.x) * g.unfix); }
-  __device__ static float im(const T& v, const Geo& g) { return (float)((double)fixed_sum(v.y) * g.unfix); }
+  __device__ static bool nonzero(const T& v) { return fixed_nonzero(v.x | v.y); }
+  __device__ static float re(const T& v, const Geo& g) { return (float)(fixed_sum(v.x) * g.unfix); }
+  __device__ static float im(const T& v, const Geo& g) { return (float)(fixed_sum(v.y) * g.unfix); }
 };
 
 // Mode-0 deposit accumulators (chi, and J_x, J_r of the Esirkepov scheme).
@@ -215,72 +232,163 @@ template <> struct Acc0<float> {
   using T = long long;
   __device__ static double scale(const Geo& g) { return g.fix0; }
   __device__ static void add_prod(T* a, double u, double x) { atomicAdd((unsigned long long*)a, fixed_bits(u, x)); }
-  __device__ static bool nonzero(T v) { return fixed_sum(v) != 0; }
-  __device__ static double val(T v, const Geo& g) { return (double)fixed_sum(v) * g.unfix0; }
+  __device__ static bool nonzero(T v) { return fixed_nonzero(v); }
+  __device__ static double val(T v, const Geo& g) { return fixed_sum(v) * g.unfix0; }
 };
 
 // Elementary functions.  The FP32 path uses the hardware reciprocal, square
 // root, reciprocal square root and sine/cosine (about 1 ulp, or ~1e-6 for
 // the direction cosines of the azimuth, far inside the FP32 path's
-// tolerance); the FP64 path uses the libm calls.
+// tolerance).  The FP64 path refines the hardware's approximations to FP64
+// and sums its own series, for the ranges met here: no scaling of extreme
+// arguments and no reduction of large angles, whose code took the position
+// pass to 169 registers (one work group per CU).
 __device__ inline float rsqrt_r(float x) { return __builtin_amdgcn_rsqf(x); }  // x >= 1 here
-__device__ inline double rsqrt_r(double x) { return rsqrt(x); }
 __device__ inline float sqrt_r(float x) { return __builtin_amdgcn_sqrtf(x); }
-__device__ inline double sqrt_r(double x) { return sqrt(x); }
 __device__ inline float rcp_r(float x) { return __builtin_amdgcn_rcpf(x); }
-__device__ inline double rcp_r(double x) { return 1.0 / x; }
+// 1 / sqrt(x), x >= 1: with e = 1 - x y^2, y (1 - e)^(-1/2) to third order
+__device__ inline double rsqrt_r(double x) {
+  const double y = __builtin_amdgcn_rsq(x);
+  const double e = fma(-(x * y), y, 1.0);
+  return fma(y * e, fma(e, 0.375, 0.5), y);
+}
+// Newton's steps for 1 / x (x not denormal; x = 0 gives a NaN)
+__device__ inline double rcp_r(double x) {
+  double y = __builtin_amdgcn_rcp(x);
+  y = fma(fma(-x, y, 1.0), y, y);
+  return fma(fma(-x, y, 1.0), y, y);
+}
+__device__ inline double sqrt_r(double x) {  // x >= 0
+  const double s = x * rsqrt_r(x);
+  return x > 0.0 ? fma(fma(-s, s, x), 0.5 * rcp_r(s), s) : 0.0;
+}
 __device__ inline void sincos_r(float t, float* s, float* c) {
   *s = __sinf(t);
   *c = __cosf(t);
 }
-__device__ inline void sincos_r(double t, double* s, double* c) { sincos(t, s, c); }
-// azimuth increment atan2(b, ra); in FP32, for ra > 0 and |b/ra| < 0.05 the
-// odd series beta - beta^3/3 + beta^5/5 (truncation below beta^7/7 < 1.2e-10,
-// under the FP32 resolution of the azimuth)
-__device__ inline float dtheta(float b, float ra) {
-  if (ra > 0.0f) {
-    const float beta = b * rcp_r(ra);
-    if (fabsf(beta) < 0.05f) {
-      const float b2 = beta * beta;
-      return beta * (1.0f - b2 * (1.0f / 3.0f - b2 * 0.2f));
-    }
-  }
-  return atan2f(b, ra);
+// |t| at most a few turns: t - n pi/2 with pi/2 in two parts, Taylor series
+// of the remainder (at most pi/4; the first omitted terms are below 1e-17)
+__device__ inline void sincos_r(double t, double* sn, double* cs) {
+  const double n = rint(t * 0.63661977236758134308);
+  double r = fma(-n, 1.57079632679489661923, t);
+  r = fma(-n, 6.12323399573676603587e-17, r);
+  const double z = r * r;
+  double a = 1.0 / 355687428096000.0;  // 1/17!
+  a = fma(a, z, -1.0 / 1307674368000.0);
+  a = fma(a, z, 1.0 / 6227020800.0);
+  a = fma(a, z, -1.0 / 39916800.0);
+  a = fma(a, z, 1.0 / 362880.0);
+  a = fma(a, z, -1.0 / 5040.0);
+  a = fma(a, z, 1.0 / 120.0);
+  a = fma(a, z, -1.0 / 6.0);
+  const double s = fma(a * z, r, r);
+  double b = 1.0 / 20922789888000.0;  // 1/16!
+  b = fma(b, z, -1.0 / 87178291200.0);
+  b = fma(b, z, 1.0 / 479001600.0);
+  b = fma(b, z, -1.0 / 3628800.0);
+  b = fma(b, z, 1.0 / 40320.0);
+  b = fma(b, z, -1.0 / 720.0);
+  b = fma(b, z, 1.0 / 24.0);
+  b = fma(b, z, -0.5);
+  const double c = fma(b, z, 1.0);
+  const int q = (int)n;
+  const double u = (q & 1) ? c : s, v = (q & 1) ? s : c;
+  *sn = (q & 2) ? -u : u;
+  *cs = ((q + 1) & 2) ? -v : v;
 }
-__device__ inline double dtheta(double b, double ra) { return atan2(b, ra); }
+// Series in b2 = beta^2 for |beta| < SMALL_BETA, the displacement of a step
+// against its radius: (sqrt(1 + b2) - 1) / b2, 1 / sqrt(1 + b2) and
+// atan(beta) / beta, to the rounding of the type (binomial and arctangent
+// series; the first omitted terms are below 6e-10 and 5e-17 of the sum).
+// They replace a square root, a reciprocal square root and two reciprocals
+// per particle; only waves with a lane closer to the axis take the general
+// forms.
+constexpr double SMALL_BETA = 0.05;
+__device__ inline float sqrt1_series(float b2) { return fmaf(b2, fmaf(b2, 0.0625f, -0.125f), 0.5f); }
+__device__ inline double sqrt1_series(double b2) {
+  double s = -21.0 / 1024;
+  s = fma(b2, s, 7.0 / 256);
+  s = fma(b2, s, -5.0 / 128);
+  s = fma(b2, s, 1.0 / 16);
+  s = fma(b2, s, -1.0 / 8);
+  return fma(b2, s, 0.5);
+}
+__device__ inline float rhyp_series(float b2) { return fmaf(b2, fmaf(b2, 0.375f, -0.5f), 1.0f); }
+__device__ inline double rhyp_series(double b2) {
+  double s = -63.0 / 256;
+  s = fma(b2, s, 35.0 / 128);
+  s = fma(b2, s, -5.0 / 16);
+  s = fma(b2, s, 3.0 / 8);
+  s = fma(b2, s, -0.5);
+  return fma(b2, s, 1.0);
+}
+__device__ inline float atan_series(float b2) { return fmaf(-b2, fmaf(-b2, 0.2f, 1.0f / 3.0f), 1.0f); }
+__device__ inline double atan_series(double b2) {
+  double s = 1.0 / 13;
+  s = fma(-b2, s, 1.0 / 11);
+  s = fma(-b2, s, 1.0 / 9);
+  s = fma(-b2, s, 1.0 / 7);
+  s = fma(-b2, s, 1.0 / 5);
+  s = fma(-b2, s, 1.0 / 3);
+  return fma(-b2, s, 1.0);
+}
+__device__ inline float dtheta(float b, float ra) { return atan2f(b, ra); }
+// atan2(b, ra) by halving the angle (tan(x/2) = sin x / (1 + cos x)) four
+// times, to at most pi/32, and the series
+__device__ inline double dtheta(double b, double ra) {
+  const double h = sqrt_r(ra * ra + b * b);
+  if (!(h > 0.0)) return 0.0;
+  double t = fabs(b) * rcp_r(h + fabs(ra));  // tan of half the angle to the nearer end of the axis
+#pragma unroll 1
+  for (int k = 0; k < 3; ++k) t *= rcp_r(1.0 + sqrt_r(fma(t, t, 1.0)));
+  const double t2 = t * t;
+  double s = -1.0 / 15;
+  s = fma(t2, s, 1.0 / 13);
+  s = fma(t2, s, -1.0 / 11);
+  s = fma(t2, s, 1.0 / 9);
+  s = fma(t2, s, -1.0 / 7);
+  s = fma(t2, s, 1.0 / 5);
+  s = fma(t2, s, -1.0 / 3);
+  double x = 16.0 * fma(t2 * s, t, t);
+  x = ra < 0.0 ? 3.14159265358979323846 - x : x;
+  return copysign(x, b);
+}
 
 // carry an offset back into [0, 1): cell += floor(off), off -= floor(off)
 template <class R> __device__ inline void carry(int& cell, R& off) {
-  const R c = floor(off);
-  cell += (int)c;
-  off -= c;
-  if (off >= (R)1) {  // rounding of 1 - tiny
-    off = 0;
-    cell += 1;
-  }
+  cell += floor_int(off);
+  off = fract_r(off);
 }
 
 // New radius and azimuth after a Cartesian transverse displacement with
 // radial component a and azimuthal component b (lengths) from radius r:
 // r' = |(r + a, b)|, written r' - r = a + (r + a)(sqrt(1 + beta^2) - 1) with
 // beta = b/(r + a) so that small displacements keep full relative precision.
-template <class R> __device__ inline void radial_step(R r, R a, R b, R& dr_out, R& dth) {
+// Returns whether |beta| < SMALL_BETA with r + a > 0: the displacement's
+// mid-point has then an even smaller beta, (b/2)/(r + a/2).
+template <class R> __device__ inline bool radial_step(R r, R a, R b, R& dr_out, R& dth) {
   const R ra = r + a;
+  const R beta = b * rcp_r(ra);
+  if (ra > (R)0 && fabs(beta) < (R)SMALL_BETA) {
+    const R b2 = beta * beta;
+    dr_out = fma(b * beta, sqrt1_series(b2), a);
+    dth = beta * atan_series(b2);
+    return true;
+  }
   if (ra > (R)0) {
-    const R beta = b * rcp_r(ra);
     const R q = sqrt_r((R)1 + beta * beta);
     dr_out = a + ra * beta * beta * rcp_r((R)1 + q);
   } else {
     dr_out = sqrt_r(ra * ra + b * b) - r;
   }
   dth = dtheta(b, ra);
+  return false;
 }
 
+// t (less than a turn beyond the range) brought back into [-pi, pi]
 template <class R> __device__ inline R wrap_angle(R t) {
-  const R pi = (R)3.14159265358979323846, two_pi = (R)6.28318530717958647692;
-  if (t > pi) t -= two_pi;
-  if (t < -pi) t += two_pi;
-  return t;
+  const R two_pi = (R)6.28318530717958647692, inv = (R)0.15915494309189533577;
+  return fma(-rint(t * inv), two_pi, t);
 }
 
 // Access to the particle records.  Each pass reads and writes a record once;
@@ -528,7 +636,7 @@ __global__ __launch_bounds__(WG, (mom_waves_per_simd<R, DEFER, SCAT, O>())) void
   // derivative on the axis, odd below it).  A scattering pass with quadratic
   // shapes stages it (the outermost ring of the region is unused); the
   // other gathers form it from the staged Phi (below).
-  const R i2dx = (R)(0.5 / g.dx), i2dr = (R)(0.5 / g.dr);
+  const R i2dx = (R)(0.5 * g.rdx), i2dr = (R)(0.5 * g.rdr);
   if constexpr (O == 2 && SCAT != SCAT_NONE) {
     for (int k = threadIdx.x; k < RN; k += WG) {
       const int a = k / RL, b = k - (k / RL) * RL;
@@ -864,10 +972,12 @@ template <class R, bool M1> struct SmemPos {
 // (radial a, azimuthal b, lengths) at the old azimuth, new azimuth, velocity
 template <class R> struct Move {
   int ix0, jr0, ix1, jr1;
+  int dix, djr;  // steps in cells, -1, 0 or 1 (less than a cell: dt < dx, dt < dr)
   R fx0, fr0, fx1, fr1;
   R th0, th1, a, b;
   R c0, s0;  // cos, sin of the old azimuth
   bool refl;
+  bool small;  // not reflected, and the step is short against its radius (radial_step)
   R vx, vy, vz;
 };
 
@@ -885,9 +995,11 @@ __device__ inline void push_position(const Geo& g, unsigned cw, R fx, R fr, R th
   mv.vx = vx;
   mv.vy = vy;
   mv.vz = vz;
-  mv.ix1 = mv.ix0;
-  mv.fx1 = fx + vx * (R)(g.dt / g.dx);
-  carry(mv.ix1, mv.fx1);
+  // (|v| <= 1, so the floors below are -1, 0 or 1, whatever the state)
+  const R x1 = fma(vx, (R)g.dtdx, fx);
+  mv.dix = floor_int(x1);
+  mv.ix1 = mv.ix0 + mv.dix;
+  mv.fx1 = fract_r(x1);
   R s, c;
   sincos_r(th, &s, &c);
   mv.c0 = c;
@@ -897,20 +1009,19 @@ __device__ inline void push_position(const Geo& g, unsigned cw, R fx, R fr, R th
   mv.b = -s * dy + c * dz;
   const R r = ((R)mv.jr0 + fr) * dr;
   R drad, dth;
-  radial_step(r, mv.a, mv.b, drad, dth);
-  mv.jr1 = mv.jr0;
-  mv.fr1 = fr + drad * (R)(1.0 / g.dr);
-  carry(mv.jr1, mv.fr1);
-  if (mv.jr1 < 0) {
-    mv.jr1 = 0;
-    mv.fr1 = 0;
-  }
+  mv.small = radial_step(r, mv.a, mv.b, drad, dth);
+  // (the radius stays >= 0 whatever the rounding)
+  const R r1 = clamp_r(fma(drad, (R)g.rdr, fr), max((R)-1, -(R)mv.jr0), (R)1.875);
+  mv.djr = floor_int(r1);
+  mv.jr1 = mv.jr0 + mv.djr;
+  mv.fr1 = fract_r(r1);
   mv.th1 = wrap_angle(th + dth);
   mv.refl = false;
   if (mv.jr1 >= g.nr) {
     // r' = r_max + e with 0 <= e < dr  ->  r_max - e; reverse p_r
     const R e = (R)(mv.jr1 - g.nr) + mv.fr1;
     mv.jr1 = g.nr - 1;
+    mv.djr = min(max(mv.jr1 - mv.jr0, -1), 1);
     mv.fr1 = (R)1 - e;
     if (mv.fr1 < (R)0) mv.fr1 = 0;
     R s1, c1;
@@ -919,7 +1030,47 @@ __device__ inline void push_position(const Geo& g, unsigned cw, R fx, R fr, R th
     py -= (R)2 * prad * c1;
     pz -= (R)2 * prad * s1;
     mv.refl = true;
+    mv.small = false;
   }
+}
+
+// The Cartesian mid-point of a move, where mode 1 deposits, in the frame of
+// the old azimuth at (r0 + a/2, b/2) (from both end points when the particle
+// was reflected): its row as a step from the old one (at most one, as the
+// move is shorter than a cell), its offset in that row, the cosine and sine
+// of its azimuth.
+template <class R>
+__device__ inline void mid_point(const Geo& g, const Move<R>& mv, int& djm, R& frm, R& c, R& s) {
+  const R dr = (R)g.dr, rdr = (R)g.rdr;
+  const R r0 = ((R)mv.jr0 + mv.fr0) * dr;
+  const R u = r0 + (R)0.5 * mv.a, v = (R)0.5 * mv.b;
+  R f;
+  if (mv.small) {
+    const R beta = v * rcp_r(u), b2 = beta * beta;
+    const R cd = rhyp_series(b2), sd = beta * cd;
+    f = fma(fma(v * beta, sqrt1_series(b2), (R)0.5 * mv.a), rdr, mv.fr0);
+    c = mv.c0 * cd - mv.s0 * sd;
+    s = mv.s0 * cd + mv.c0 * sd;
+  } else if (!mv.refl) {
+    const R rm = sqrt_r(u * u + v * v);
+    const R cd = rm > (R)0 ? u / rm : (R)1, sd = rm > (R)0 ? v / rm : (R)0;
+    // (for u > 0 the radius by its small difference from u)
+    f = u > (R)0 ? mv.fr0 + ((R)0.5 * mv.a + v * v / (u + rm)) * rdr : mv.fr0 + (rm - r0) * rdr;
+    c = mv.c0 * cd - mv.s0 * sd;
+    s = mv.s0 * cd + mv.c0 * sd;
+  } else {
+    R s1, c1;
+    sincos_r(mv.th1, &s1, &c1);
+    const R r1 = ((R)mv.jr1 + mv.fr1) * dr;
+    const R ym = (R)0.5 * (r0 * mv.c0 + r1 * c1), zm = (R)0.5 * (r0 * mv.s0 + r1 * s1);
+    const R rm = sqrt_r(ym * ym + zm * zm);
+    f = mv.fr0 + (rm - r0) * rdr;
+    c = rm > (R)0 ? ym / rm : (R)1;
+    s = rm > (R)0 ? zm / rm : (R)0;
+  }
+  f = clamp_r(f, max((R)-1, -(R)mv.jr0), (R)1.875);
+  djm = floor_int(f);
+  frm = fract_r(f);
 }
 
 // Esirkepov current of one particle between two positions (mode 0) and the
@@ -928,109 +1079,70 @@ template <class R, bool M1>
 __device__ inline void deposit_current(SmemPos<R, M1>& sm, const Region& q, const Geo& g, const Move<R>& mv, R w,
                                        bool& bad) {
   // the stencil spans min(a0, a1) .. min(a0, a1) + 2: the push moves a
-  // particle less than a cell (dt < dx and dt < dr, checked at init), so the
-  // new cell is the old one's neighbour or itself; that step, bounded to one
-  // cell, keeps every index inside the region once the old cell is
-  const int a0 = clampi(mv.ix0 - q.X0, 1, LX - 4, bad);
-  const int a1 = a0 + min(max(mv.ix1 - mv.ix0, -1), 1);
-  const int b0 = clampi(mv.jr0 - q.R0, 1, LR - 4, bad);
-  const int b1 = b0 + min(max(mv.jr1 - mv.jr0, -1), 1);
-  // node weights on the 3-node union of the old and new supports, without
-  // indexing into register arrays: d = a1 - a0 in {-1, 0, 1}
-  const int dxs = a1 - a0, drs = b1 - b0;
+  // particle less than a cell, so the new cell is the old one's neighbour or
+  // itself, and every index is inside the region once the old cell is
+  const int a0 = clampi(mv.ix0 - q.X0, 2, LX - 4, bad);
+  const int b0 = clampi(mv.jr0 - q.R0, 2, LR - 4, bad);
+  const int dxs = mv.dix, drs = mv.djr;
+  // On the 3-node union of the old and new supports (first node amin), with
+  // F0 and F1 the weights that the old and new position put beyond the first
+  // node, the first partial sum of the flux along an axis is F0 - F1 and the
+  // node sums S0 + S1 are 2 - (F0 + F1), (F0 + F1) - T2, T2.  The second
+  // partial sum and the third node exist only when the particle changed
+  // column (row).
   const int amin = a0 + min(dxs, 0), bmin = b0 + min(drs, 0);
-  const R u0 = (R)1 - mv.fx0, u1 = (R)1 - mv.fx1, v0 = (R)1 - mv.fr0, v1 = (R)1 - mv.fr1;
-  const R S0x[3] = {dxs >= 0 ? u0 : (R)0, dxs >= 0 ? mv.fx0 : u0, dxs >= 0 ? (R)0 : mv.fx0};
-  const R S1x[3] = {dxs <= 0 ? u1 : (R)0, dxs <= 0 ? mv.fx1 : u1, dxs <= 0 ? (R)0 : mv.fx1};
-  const R S0r[3] = {drs >= 0 ? v0 : (R)0, drs >= 0 ? mv.fr0 : v0, drs >= 0 ? (R)0 : mv.fr0};
-  const R S1r[3] = {drs <= 0 ? v1 : (R)0, drs <= 0 ? mv.fr1 : v1, drs <= 0 ? (R)0 : mv.fr1};
-  // J_x (i+1/2, j): flux accumulated along x; the third partial sum is zero
-  const R cx0 = S1x[0] - S0x[0], cx1 = cx0 + S1x[1] - S0x[1];
-  const R cr0 = S1r[0] - S0r[0], cr1 = cr0 + S1r[1] - S0r[1];
+  const R F0x = dxs < 0 ? (R)1 : mv.fx0, F1x = dxs > 0 ? (R)1 : mv.fx1;
+  const R F0r = drs < 0 ? (R)1 : mv.fr0, F1r = drs > 0 ? (R)1 : mv.fr1;
+  const R sx = F0x + F1x, sr = F0r + F1r;
+  const R T2x = dxs > 0 ? mv.fx1 : (dxs < 0 ? mv.fx0 : (R)0), T2r = drs > 0 ? mv.fr1 : (drs < 0 ? mv.fr0 : (R)0);
+  // J_x (i+1/2, j): flux accumulated along x; J_r (i, j+1/2): along r
   // (the face areas are applied at the flush)
   using A0 = Acc0<R>;
   typename A0::T* jx = &sm.jx[amin * LR + bmin];
   typename A0::T* jr = &sm.jr[amin * LR + bmin];
-  const double hw = 0.5 * (double)w * A0::scale(g);
-  const double cx0d = cx0, cx1d = cx1, cr0d = cr0, cr1d = cr1;
-  // the second partial sum is non-zero only when the particle changed
-  // column (row); a zero first one adds nothing
-#pragma unroll
-  for (int bb = 0; bb < 3; ++bb) {
-    const double sr = (double)(S0r[bb] + S1r[bb]) * hw;
-    A0::add_prod(&jx[bb], cx0d, sr);
-    if (dxs != 0) A0::add_prod(&jx[LR + bb], cx1d, sr);
+  const double hw = (double)w * (0.5 * A0::scale(g));
+  const double cx0 = F0x - F1x, cr0 = F0r - F1r;
+  const double wr0 = (double)((R)2 - sr) * hw, wr1 = (double)(sr - T2r) * hw;
+  const double wx0 = (double)((R)2 - sx) * hw, wx1 = (double)(sx - T2x) * hw;
+  A0::add_prod(&jx[0], cx0, wr0);
+  A0::add_prod(&jx[1], cx0, wr1);
+  A0::add_prod(&jr[0], cr0, wx0);
+  A0::add_prod(&jr[LR], cr0, wx1);
+  if (dxs != 0) {
+    const double cx1 = dxs > 0 ? -mv.fx1 : mv.fx0;
+    A0::add_prod(&jx[LR], cx1, wr0);
+    A0::add_prod(&jx[LR + 1], cx1, wr1);
+    A0::add_prod(&jr[2 * LR], cr0, (double)T2x * hw);
   }
-  // J_r (i, j+1/2): flux accumulated along r
-#pragma unroll
-  for (int aa = 0; aa < 3; ++aa) {
-    const double sx = (double)(S0x[aa] + S1x[aa]) * hw;
-    A0::add_prod(&jr[aa * LR], cr0d, sx);
-    if (drs != 0) A0::add_prod(&jr[aa * LR + 1], cr1d, sx);
+  if (drs != 0) {
+    const double cr1 = drs > 0 ? -mv.fr1 : mv.fr0;
+    const double wr2 = (double)T2r * hw;
+    A0::add_prod(&jr[1], cr1, wx0);
+    A0::add_prod(&jr[LR + 1], cr1, wx1);
+    A0::add_prod(&jx[2], cx0, wr2);
+    if (dxs != 0) {
+      A0::add_prod(&jx[LR + 2], (double)(dxs > 0 ? -mv.fx1 : mv.fx0), wr2);
+      A0::add_prod(&jr[2 * LR + 1], cr1, (double)T2x * hw);
+    }
   }
   if (M1) {
-    // Cartesian mid-point of the old and new positions: in the frame of the
-    // old azimuth it sits at (r0 + a/2, b/2); its radius and direction follow
-    // without trigonometric calls
-    const R dr = (R)g.dr;
-    const R r0 = ((R)mv.jr0 + mv.fr0) * dr;
-    int jm = mv.jr0;
+    int djm;
     R frm, c, s;
-    if (!mv.refl) {
-      const R u = r0 + (R)0.5 * mv.a, v = (R)0.5 * mv.b;
-      R cd, sd;
-      if (u > (R)0) {
-        const R beta = v * rcp_r(u);
-        const R q2b = (R)1 + beta * beta;
-        cd = rsqrt_r(q2b);  // 1 / sqrt(1 + beta^2)
-        const R qq = q2b * cd;
-        frm = mv.fr0 + ((R)0.5 * mv.a + u * beta * beta * rcp_r((R)1 + qq)) * (R)(1.0 / g.dr);
-        sd = beta * cd;
-      } else {
-        const R rm = sqrt_r(u * u + v * v);
-        frm = mv.fr0 + (rm - r0) / dr;
-        cd = rm > (R)0 ? u / rm : (R)1;
-        sd = rm > (R)0 ? v / rm : (R)0;
-      }
-      c = mv.c0 * cd - mv.s0 * sd;
-      s = mv.s0 * cd + mv.c0 * sd;
-    } else {
-      R s1, c1;
-      sincos_r(mv.th1, &s1, &c1);
-      const R r1 = ((R)mv.jr1 + mv.fr1) * dr;
-      const R ym = (R)0.5 * (r0 * mv.c0 + r1 * c1), zm = (R)0.5 * (r0 * mv.s0 + r1 * s1);
-      const R rm = sqrt_r(ym * ym + zm * zm);
-      jm = 0;
-      frm = rm / dr;
-      c = rm > (R)0 ? ym / rm : (R)1;
-      s = rm > (R)0 ? zm / rm : (R)0;
-    }
-    carry(jm, frm);
-    if (jm < 0) {
-      jm = 0;
-      frm = 0;
-    }
-    if (jm > g.nr - 1) {
-      frm += (R)(jm - (g.nr - 1));
-      jm = g.nr - 1;
-    }
-    const R um = (R)0.5 * ((R)a0 + mv.fx0 + (R)a1 + mv.fx1);
-    const int am = (int)floor(um);
-    const R fm = um - (R)am;
-    const int bm = clampi(jm - q.R0, 1, LR - 3, bad);
-    const int amc = clampi(am, 1, LX - 3, bad);
-    const Lin<R> Px = primal_w<R>(amc, fm), Dx = dual_w<R>(amc, fm);
+    mid_point<R>(g, mv, djm, frm, c, s);
+    // the old cell's indices plus a step of at most one: inside the region
+    const R um = fma((R)0.5 * (R)g.dtdx, mv.vx, mv.fx0);
+    const int am = a0 + floor_int(um), bm = b0 + djm;
+    const R fm = fract_r(um);
+    const Lin<R> Px = primal_w<R>(am, fm), Dx = dual_w<R>(am, fm);
     const Lin<R> Pr = primal_w<R>(bm, frm), Dr = dual_w<R>(bm, frm);
     // 2 q w v e^{i theta} per component (electrons, q = -1), with the
     // accumulator scale folded in; radial weights times inverse volumes
-    const R q2 = (R)-2 * w * Acc1<R>::scale(g);
+    const R q2 = w * ((R)-2 * Acc1<R>::scale(g));
     const R vx = q2 * mv.vx, vr = q2 * (mv.vy * c + mv.vz * s), vt = q2 * (mv.vz * c - mv.vy * s);
     const double xc = vx * c, xs = vx * s, rc = vr * c, rs = vr * s, tc = vt * c, ts = vt * s;
     const R pv[2] = {Pr.a * sm.ivn[Pr.i], Pr.b * sm.ivn[Pr.i + 1]};
-    // J_r1 rows; row -1/2 folds onto +1/2 (even for mode 1)
-    const int dn0 = (q.R0 + Dr.i == -1) ? Dr.i + 1 : Dr.i, dn1 = Dr.i + 1;
-    const R dv[2] = {Dr.a * sm.ivh[dn0], Dr.b * sm.ivh[dn1]};
-    const int dn[2] = {dn0, dn1};
+    // (J_r1 of the half row -1/2 is folded onto +1/2 at the flush)
+    const R dv[2] = {Dr.a * sm.ivh[Dr.i], Dr.b * sm.ivh[Dr.i + 1]};
 #pragma unroll
     for (int aa = 0; aa < 2; ++aa) {
       const R wdx = aa ? Dx.b : Dx.a, wpx = aa ? Px.b : Px.a;
@@ -1038,7 +1150,7 @@ __device__ inline void deposit_current(SmemPos<R, M1>& sm, const Region& q, cons
       for (int bb = 0; bb < 2; ++bb) {
         const double ux = wdx * pv[bb], ur = wpx * dv[bb], ut = wpx * pv[bb];
         Acc1<R>::add_prod(sm.jx1, (Dx.i + aa) * LR + Pr.i + bb, ux, xc, xs);  // (i+1/2, j)
-        Acc1<R>::add_prod(sm.jr1, (Px.i + aa) * LR + dn[bb], ur, rc, rs);     // (i, j+1/2)
+        Acc1<R>::add_prod(sm.jr1, (Px.i + aa) * LR + Dr.i + bb, ur, rc, rs);  // (i, j+1/2)
         Acc1<R>::add_prod(sm.jt1, (Px.i + aa) * LR + Pr.i + bb, ut, tc, ts);  // (i, j)
       }
     }
@@ -1048,15 +1160,14 @@ __device__ inline void deposit_current(SmemPos<R, M1>& sm, const Region& q, cons
 // Order-2 currents: the Esirkepov decomposition of the change between the
 // old and new quadratic stencils on their 4-node union (mode 0), and the
 // quadratic mid-point deposit of mode 1.  Contributions to the rows below
-// the axis stay in the LDS ghost rows and are folded at the flush, except
-// the mode-1 J_r of the half row -1/2, which lands on +1/2 directly (even).
+// the axis stay in the LDS ghost rows and are folded at the flush.
 template <class R, bool M1>
 __device__ inline void deposit_current2(SmemPos<R, M1>& sm, const Region& q, const Geo& g, const Move<R>& mv, R w,
                                         bool& bad) {
   const int a0 = clampi(mv.ix0 - q.X0, 2, LX - 4, bad);
-  const int a1 = a0 + min(max(mv.ix1 - mv.ix0, -1), 1);  // (a step of at most one cell, as above)
+  const int a1 = a0 + mv.dix;  // (a step of at most one cell)
   const int b0 = clampi(mv.jr0 - q.R0, 2, LR - 4, bad);
-  const int b1 = b0 + min(max(mv.jr1 - mv.jr0, -1), 1);
+  const int b1 = b0 + mv.djr;
   const Quad<R> X0 = quad_primal<R>(a0, mv.fx0), X1 = quad_primal<R>(a1, mv.fx1);
   const Quad<R> Y0 = quad_primal<R>(b0, mv.fr0), Y1 = quad_primal<R>(b1, mv.fr1);
   // nearest nodes move by at most one (less than a cell per step)
@@ -1087,7 +1198,7 @@ __device__ inline void deposit_current2(SmemPos<R, M1>& sm, const Region& q, con
   using A0 = Acc0<R>;
   typename A0::T* jx = &sm.jx[ax * LR + by];
   typename A0::T* jr = &sm.jr[ax * LR + by];
-  const double hw = 0.5 * (double)w * A0::scale(g);
+  const double hw = (double)w * (0.5 * A0::scale(g));
 #pragma unroll
   for (int bb = 0; bb < 4; ++bb) {
     const double sr = (double)(S0r[bb] + S1r[bb]) * hw;
@@ -1103,68 +1214,25 @@ __device__ inline void deposit_current2(SmemPos<R, M1>& sm, const Region& q, con
       if (cr[bb] != (R)0) A0::add_prod(&jr[aa * LR + bb], (double)cr[bb], sx);
   }
   if (M1) {
-    // mid-point as in the linear deposit
-    const R dr = (R)g.dr;
-    const R r0 = ((R)mv.jr0 + mv.fr0) * dr;
-    int jm = mv.jr0;
+    int djm;
     R frm, c, s;
-    if (!mv.refl) {
-      const R u = r0 + (R)0.5 * mv.a, v = (R)0.5 * mv.b;
-      R cd, sd;
-      if (u > (R)0) {
-        const R beta = v * rcp_r(u);
-        const R q2b = (R)1 + beta * beta;
-        cd = rsqrt_r(q2b);  // 1 / sqrt(1 + beta^2)
-        const R qq = q2b * cd;
-        frm = mv.fr0 + ((R)0.5 * mv.a + u * beta * beta * rcp_r((R)1 + qq)) * (R)(1.0 / g.dr);
-        sd = beta * cd;
-      } else {
-        const R rm = sqrt_r(u * u + v * v);
-        frm = mv.fr0 + (rm - r0) / dr;
-        cd = rm > (R)0 ? u / rm : (R)1;
-        sd = rm > (R)0 ? v / rm : (R)0;
-      }
-      c = mv.c0 * cd - mv.s0 * sd;
-      s = mv.s0 * cd + mv.c0 * sd;
-    } else {
-      R s1, c1;
-      sincos_r(mv.th1, &s1, &c1);
-      const R r1 = ((R)mv.jr1 + mv.fr1) * dr;
-      const R ym = (R)0.5 * (r0 * mv.c0 + r1 * c1), zm = (R)0.5 * (r0 * mv.s0 + r1 * s1);
-      const R rm = sqrt_r(ym * ym + zm * zm);
-      jm = 0;
-      frm = rm / dr;
-      c = rm > (R)0 ? ym / rm : (R)1;
-      s = rm > (R)0 ? zm / rm : (R)0;
-    }
-    carry(jm, frm);
-    if (jm < 0) {
-      jm = 0;
-      frm = 0;
-    }
-    if (jm > g.nr - 1) {
-      frm += (R)(jm - (g.nr - 1));
-      jm = g.nr - 1;
-    }
-    const R um = (R)0.5 * ((R)a0 + mv.fx0 + (R)a1 + mv.fx1);
-    const int am = (int)floor(um);
-    const R fm = um - (R)am;
-    const int bm = clampi(jm - q.R0, 1, LR - 3, bad);
-    const int amc = clampi(am, 1, LX - 3, bad);
-    const Quad<R> Qx = quad_primal<R>(amc, fm), Ux = quad_dual<R>(amc, fm);
+    mid_point<R>(g, mv, djm, frm, c, s);
+    const R um = fma((R)0.5 * (R)g.dtdx, mv.vx, mv.fx0);
+    const int am = a0 + floor_int(um), bm = b0 + djm;
+    const R fm = fract_r(um);
+    const Quad<R> Qx = quad_primal<R>(am, fm), Ux = quad_dual<R>(am, fm);
     const Quad<R> Qr = quad_primal<R>(bm, frm), Ur = quad_dual<R>(bm, frm);
-    const R q2 = (R)-2 * w * Acc1<R>::scale(g);
+    const R q2 = w * ((R)-2 * Acc1<R>::scale(g));
     const R vx = q2 * mv.vx, vr = q2 * (mv.vy * c + mv.vz * s), vt = q2 * (mv.vz * c - mv.vy * s);
     const double xc = vx * c, xs = vx * s, rc = vr * c, rs = vr * s, tc = vt * c, ts = vt * s;
     // radial weights times the inverse volume of the row they land on (the
-    // primal ghost row carries row 1's); the half row -1/2 is row +1/2
+    // ghost rows carry their mirrors'; their deposits are folded onto those
+    // at the flush)
     R pv[3], dv[3];
-    int dn[3];
 #pragma unroll
     for (int bb = 0; bb < 3; ++bb) {
       pv[bb] = Qr.w[bb] * sm.ivn[Qr.i + bb];
-      dn[bb] = (q.R0 + Ur.i + bb == -1) ? Ur.i + bb + 1 : Ur.i + bb;
-      dv[bb] = Ur.w[bb] * sm.ivh[dn[bb]];
+      dv[bb] = Ur.w[bb] * sm.ivh[Ur.i + bb];
     }
     // each radial factor times the velocity's cosine and sine parts in FP64,
     // then one FMA per word with the axial weight (converted once per node)
@@ -1176,7 +1244,7 @@ __device__ inline void deposit_current2(SmemPos<R, M1>& sm, const Region& q, con
       for (int aa = 0; aa < 3; ++aa) {
         const double ux = Ux.w[aa], qx = Qx.w[aa];
         Acc1<R>::add_prod(sm.jx1, (Ux.i + aa) * LR + Qr.i + bb, ux, pxc, pxs);  // (i+1/2, j)
-        Acc1<R>::add_prod(sm.jr1, (Qx.i + aa) * LR + dn[bb], qx, drc, drs);     // (i, j+1/2)
+        Acc1<R>::add_prod(sm.jr1, (Qx.i + aa) * LR + Ur.i + bb, qx, drc, drs);  // (i, j+1/2)
         Acc1<R>::add_prod(sm.jt1, (Qx.i + aa) * LR + Qr.i + bb, qx, ptc, pts);  // (i, j)
       }
     }
@@ -1185,18 +1253,28 @@ __device__ inline void deposit_current2(SmemPos<R, M1>& sm, const Region& q, con
 
 template <class R, bool M1>
 __device__ inline void stage_pos_constants(SmemPos<R, M1>& sm, const Region& q, const Geo& g) {
+  // one constant per wavefront (of the first four), so that no wavefront
+  // computes more than one FP64 division
   const double pi = 3.14159265358979323846;
-  for (int k = threadIdx.x; k < LR; k += WG) {
-    const int j = q.R0 + k;
+  const int what = threadIdx.x >> 6, k = threadIdx.x & 63;
+  static_assert(LR <= 64 && WG >= 256, "one wavefront per constant");
+  if (k >= LR || what > 3) return;
+  const int j = q.R0 + k;
+  const bool node = j >= 0 && j <= g.nr, half = j >= 0 && j <= g.nr - 1;
+  if (what == 0) {
     // 1 / (face area * dt): axial face of row j (V_j / dx), radial face at r_{j+1/2}
-    double ax = (j == 0 ? pi * g.dr * g.dr * 0.25 : 2.0 * pi * j * g.dr * g.dr);
-    double ar = 2.0 * pi * (j + 0.5) * g.dr * g.dx;
-    sm.iax[k] = (j >= 0 && j <= g.nr) ? (R)(1.0 / (ax * g.dt)) : (R)0;
-    sm.iar[k] = (j >= 0 && j <= g.nr - 1) ? (R)(1.0 / (ar * g.dt)) : (R)0;
+    const double ax = (j == 0 ? pi * g.dr * g.dr * 0.25 : 2.0 * pi * j * g.dr * g.dr);
+    sm.iax[k] = node ? (R)(1.0 / (ax * g.dt)) : (R)0;
+  } else if (what == 1) {
+    const double ar = 2.0 * pi * (j + 0.5) * g.dr * g.dx;
+    sm.iar[k] = half ? (R)(1.0 / (ar * g.dt)) : (R)0;
+  } else if (what == 2) {
     // the primal ghost row j = -1 carries the volume of row 1, onto which
     // its (order-2) deposits are folded
-    sm.ivn[k] = (j >= 0 && j <= g.nr) ? inv_vol_node<R>(g, j) : (j == -1 ? inv_vol_node<R>(g, 1) : (R)0);
-    sm.ivh[k] = (j >= 0 && j <= g.nr - 1) ? inv_vol_half<R>(g, j) : (R)0;
+    sm.ivn[k] = node ? inv_vol_node<R>(g, j) : (j == -1 ? inv_vol_node<R>(g, 1) : (R)0);
+  } else {
+    // (the ghost half row -1/2 that of +1/2)
+    sm.ivh[k] = half ? inv_vol_half<R>(g, j) : (j == -1 ? inv_vol_half<R>(g, 0) : (R)0);
   }
 }
 
@@ -1226,7 +1304,8 @@ template <class T> __device__ inline T acc_axpy(T a, const T& b, int sg) {
 // O = 2: the deposits on the rows below the axis are folded onto their
 // mirrors with the component's parity (R23): J_x row -1 onto row 1 (even for
 // mode 0, odd for mode 1), J_r face -1/2 onto +1/2 (odd for mode 0), mode-1
-// J_theta row -1 onto row 1 (even).
+// J_theta row -1 onto row 1 (even), and, for both orders, mode-1 J_r face
+// -1/2 onto +1/2 (even).
 template <class R, bool M1, int O>
 __device__ inline void flush_current(SmemPos<R, M1>& sm, const Region& q, const Geo& g, R* jx_out,
                                      R* jr_out, typename cplx_of<R>::type* jx1_out,
@@ -1256,9 +1335,11 @@ __device__ inline void flush_current(SmemPos<R, M1>& sm, const Region& q, const 
           atomicAdd(&jx1_out[o].x, (R)A::re(v1x, g));
           atomicAdd(&jx1_out[o].y, (R)A::im(v1x, g));
         }
-        if (drok && A::nonzero(sm.jr1[k])) {
-          atomicAdd(&jr1_out[o].x, (R)A::re(sm.jr1[k], g));
-          atomicAdd(&jr1_out[o].y, (R)A::im(sm.jr1[k], g));
+        typename A::T v1r = sm.jr1[k];
+        if (j == 0 && b >= 1) v1r = acc_axpy(v1r, sm.jr1[k - 1], 1);
+        if (drok && A::nonzero(v1r)) {
+          atomicAdd(&jr1_out[o].x, (R)A::re(v1r, g));
+          atomicAdd(&jr1_out[o].y, (R)A::im(v1r, g));
         }
         if (A::nonzero(v1t)) {
           atomicAdd(&jt1_out[o].x, (R)A::re(v1t, g));
@@ -1274,9 +1355,11 @@ __device__ inline void flush_current(SmemPos<R, M1>& sm, const Region& q, const 
           atomicAdd(&jx1_out[o].x, (R)A::re(sm.jx1[k], g));
           atomicAdd(&jx1_out[o].y, (R)A::im(sm.jx1[k], g));
         }
-        if (drok && A::nonzero(sm.jr1[k])) {
-          atomicAdd(&jr1_out[o].x, (R)A::re(sm.jr1[k], g));
-          atomicAdd(&jr1_out[o].y, (R)A::im(sm.jr1[k], g));
+        typename A::T v1r = sm.jr1[k];
+        if (j == 0 && b >= 1) v1r = acc_axpy(v1r, sm.jr1[k - 1], 1);
+        if (drok && A::nonzero(v1r)) {
+          atomicAdd(&jr1_out[o].x, (R)A::re(v1r, g));
+          atomicAdd(&jr1_out[o].y, (R)A::im(v1r, g));
         }
         if (A::nonzero(sm.jt1[k])) {
           atomicAdd(&jt1_out[o].x, (R)A::re(sm.jt1[k], g));
@@ -1454,7 +1537,7 @@ __device__ void inject_block(const InjectArgs& ia, Parts<R> P, const Layout& L, 
 // The FP32 quadratic pass is held to six waves per SIMD (80 registers per
 // lane, the count the LDS allows), at the price of 12 bytes of spills per
 // lane.
-template <class R, int O> constexpr int pos_waves_per_simd() { return (sizeof(R) == 4 && O == 2) ? 6 : 1; }
+template <class R, int O> constexpr int pos_waves_per_simd() { return sizeof(R) == 8 ? 4 : (O == 2 ? 6 : 1); }
 
 template <class R, bool M1, bool DEFER, int O, bool NT>
 __global__ __launch_bounds__(WG, (pos_waves_per_simd<R, O>())) void k_position(Geo g, Grids<R> f, R* __restrict__ jx_out,
@@ -1548,8 +1631,8 @@ __global__ __launch_bounds__(WG, (pos_waves_per_simd<R, O>())) void k_position(G
     } else {
       // the old cell is at most two cells out of the tile: the range of the
       // current stencil's old cell, the same clamp as the deposit's (shared)
-      const int a = clampi(cell_ix(cw) - q.X0, 1, LX - 4, bad);
-      const int b = clampi(cell_jr(cw) - q.R0, 1, LR - 4, bad);
+      const int a = clampi(cell_ix(cw) - q.X0, 2, LX - 4, bad);
+      const int b = clampi(cell_jr(cw) - q.R0, 2, LR - 4, bad);
       ph = interp2<R>(sm.phh, primal_w<R>(a, fx), primal_w<R>(b, fr));
     }
     const R ig = rsqrt_r((R)1 + px * px + py * py + pz * pz + ph);
@@ -1591,9 +1674,12 @@ __global__ __launch_bounds__(WG, (pos_waves_per_simd<R, O>())) void k_position(G
       atomicAdd(&sm.ccell[sx * CR + sr], 1);
     } else if (sc.mode == SCAT_TILE) {
       // a particle that changes tile (rare) counts for its new tile
-      const int dtx = clampi(mv.ix1 / TX - q.T, -1, 1, bad);
-      const int dtr = clampi(mv.jr1 / TR - q.tcr, -1, 1, bad);
-      if (dtx != 0 || dtr != 0) atomicAdd(&sm.tcnt[(dtx + 1) * 3 + dtr + 1], 1);
+      const int tx = mv.ix1 - q.T * TX, tr = mv.jr1 - q.tcr * TR;
+      if ((unsigned)tx >= (unsigned)TX || (unsigned)tr >= (unsigned)TR) {
+        const int dtx = clampi((tx + TX) / TX - 1, -1, 1, bad);
+        const int dtr = clampi((tr + TR) / TR - 1, -1, 1, bad);
+        atomicAdd(&sm.tcnt[(dtx + 1) * 3 + dtr + 1], 1);
+      }
     }
   }
   if (bad) atomicOr(err, ERR_HALO);
