@@ -944,11 +944,19 @@ template <class R> struct SimT : envpic_sim {
     std::vector<int4> items(ni);
     if (ni && (rc = hip_check(hipMemcpyAsync(items.data(), S.lay[lay].items, ni * sizeof(int4), hipMemcpyDeviceToHost, stream), "items"))) return rc;
     if ((rc = hip_check(hipStreamSynchronize(stream), "sync"))) return rc;
+    std::vector<int> ovb(sz.ntiles);
+    if ((rc = hip_check(hipMemcpyAsync(ovb.data(), S.lay[lay].ovb, ovb.size() * sizeof(int), hipMemcpyDeviceToHost, stream), "overflow"))) return rc;
+    if ((rc = hip_check(hipStreamSynchronize(stream), "sync"))) return rc;
     used = 0;
-    for (const int4& it : items) used = std::max(used, it.y + it.z);
+    for (const int4& it : items) {
+      used = std::max(used, it.y + it.z);
+      if (it.w > 0) used = std::max(used, ovb[it.x] + it.w);
+    }
     covered.assign(used, 0);
-    for (const int4& it : items)
+    for (const int4& it : items) {
       for (int k = it.y; k < it.y + it.z; ++k) covered[k] = 1;
+      for (int k = 0; k < it.w; ++k) covered[ovb[it.x] + k] = 1;
+    }
     return ENVPIC_OK;
   }
 

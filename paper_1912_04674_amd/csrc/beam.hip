@@ -64,8 +64,8 @@ __global__ __launch_bounds__(BG) void k_beam_hist(Parts<R> P, Layout L, BeamArgs
   const int item = blockIdx.x;
   if (item < *L.n_items) {
     const int4 it = L.items[item];
-    for (int k = threadIdx.x; k < it.z; k += BG) {
-      const int p = it.y + k;
+    for (int k = threadIdx.x; k < it.z + it.w; k += BG) {
+      const int p = item_slot(L, it, k);
       if (P.cell[p] == kDead) continue;
       const int bin = energy_bin(a, kin_energy((double)P.px[p], (double)P.py[p], (double)P.pz[p]));
       if (bin < 0) continue;
@@ -195,8 +195,8 @@ __global__ __launch_bounds__(BG) void k_beam_moments(Geo g, Parts<R> P, Layout L
   const double pym = b.st[BS_PYMEAN], pzm = b.st[BS_PZMEAN];
   if (item < *L.n_items) {
     const int4 it = L.items[item];
-    for (int k = threadIdx.x; k < it.z; k += BG) {
-      const int p = it.y + k;
+    for (int k = threadIdx.x; k < it.z + it.w; k += BG) {
+      const int p = item_slot(L, it, k);
       const unsigned cw = P.cell[p];
       if (cw == kDead) continue;
       const double px = P.px[p], py = P.py[p], pz = P.pz[p];

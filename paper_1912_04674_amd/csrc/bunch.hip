@@ -60,8 +60,8 @@ __global__ __launch_bounds__(SB) void k_bunch_charge(Geo g, Parts<R> P, Layout L
   const int item = blockIdx.x;
   if (item >= *L.n_items) return;
   const int4 it = L.items[item];
-  for (int k = threadIdx.x; k < it.z; k += SB) {
-    const int p = it.y + k;
+  for (int k = threadIdx.x; k < it.z + it.w; k += SB) {
+    const int p = item_slot(L, it, k);
     const unsigned cw = P.cell[p];
     if (cw == kDead) continue;
     const unsigned id = P.id[p];

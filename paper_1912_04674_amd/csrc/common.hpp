@@ -59,6 +59,11 @@ constexpr int LAYOUT_GATHER = 2;
 constexpr int ENTERING_TILES = (SORT_EVERY * CELL_SORT_EVERY + TX - 1) / TX + 1;
 constexpr int WG = 512;     // work-group size of the particle kernels
 constexpr int CHUNK = 4096; // largest work item (particles); small runs use smaller items
+// A tile's overflow range of at most this many particles rides with the
+// tile's last work item instead of making one of its own, which would stage
+// the tile's region and flush its deposits once more.  (The fixed-point
+// sums hold items of CHUNK + MAX_RIDERS particles.)
+constexpr int MAX_RIDERS = 1024;
 // Tile segments and their work items start at multiples of SLOT_ALIGN slots, a
 // wavefront's worth: 256 bytes of a 4-byte record array, two whole cache
 // lines.  A record access that straddles a third line costs both particle
@@ -158,13 +163,18 @@ struct Layout {
   int* offsets;  // [ntiles + 1]
   int* ext;      // [ntiles] slots in use at the start of each segment
   int* cursor;   // [ntiles] scatter cursors (full) or arrival tickets (incremental)
-  int* ovb;      // [ntiles] first overflow slot of each tile's arrivals (incremental)
+  int* ovb;      // [ntiles] first overflow slot of each tile's arrivals (incremental sorts)
   int* ovn;      // [ntiles] arrivals of each tile that go to its overflow range (incremental)
-  int4* items;   // {key, start, count, 0}
+  int4* items;   // {key, start, count, riders}: riders particles from ovb[key] on come after the count
   int* n_items;  // scalar
   int* fill;     // scalar: end of the used slots (injected columns are appended here)
   int* mode;     // scalar: LAYOUT_MOVE or LAYOUT_FULL (tile sorts)
 };
+
+// slot of the k-th particle of a work item (its range, then its riders)
+__device__ inline int item_slot(const Layout& L, const int4& it, int k) {
+  return k < it.z ? it.y + k : L.ovb[it.x] + k - it.z;
+}
 
 // The copy back after a tile sort that rebuilt its layout (settle_copy):
 // from the other buffer into the one in use, over the used slots of L, by

@@ -488,7 +488,7 @@ template <int H> struct Halo {
 // shapes (their registers are the tighter limit); the others difference the
 // staged Phi where they read it.  The sort counters exist only in the
 // scattering variants.
-template <class R, bool M1, int H, int O, bool SC> struct SmemMom {
+template <class R, bool M1, int H, int O, bool SC, bool CS> struct SmemMom {
   using C = typename cplx_of<R>::type;
   static constexpr int N = Halo<H>::N;
   static constexpr int NG = (O == 2 && SC) ? N : 1;
@@ -497,9 +497,8 @@ template <class R, bool M1, int H, int O, bool SC> struct SmemMom {
   C ex1[M1 ? N : 1], er1[M1 ? N : 1], et1[M1 ? N : 1];
   C bx1[M1 ? N : 1], br1[M1 ? N : 1], bt1[M1 ? N : 1];
   R ivol[Halo<H>::R];
-  int ccell[SC ? CRN : 1];  // sort: particles per destination cell, then their first slot
+  int ccell[CS ? CRN : 1];  // cell sort: particles per destination cell, then their next rank
 };
-constexpr int PPT = CHUNK / WG;  // particles per thread of a work item
 
 // Work item of work group b (of n groups).  Work groups are dealt to the 8
 // XCDs in turn; runs of XG consecutive items (radially adjacent tiles, whose
@@ -520,28 +519,32 @@ __device__ inline int wave_sum_i(int v) {
   return v;
 }
 
-// Rank of this lane among the lanes of its wavefront with the same slot
-// (slot < 0: none), added to a counter per slot with one LDS atomic per
-// distinct slot in the wavefront.  The lanes of a wavefront mostly share
-// one destination, which a per-lane atomic serialises on one LDS word.
-// Ranks follow lane order within a slot.  Call from wavefront-uniform
-// control flow.
-__device__ inline int wave_slot_rank(int slot, int* counters) {
+// A ticket per lane from the global counter of its key (key < 0: none), with
+// one atomic per distinct key in the wavefront; tickets follow lane order
+// within a key.  Call from wavefront-uniform control flow.
+__device__ inline int wave_ticket(int key, int* counters) {
   const int lane = (int)__lane_id();
   const unsigned long long below = (1ull << lane) - 1ull;
-  unsigned long long pending = __ballot(slot >= 0);
-  int rank = 0;
+  unsigned long long pending = __ballot(key >= 0);
+  int ticket = 0;
   while (pending) {
     const int leader = __ffsll((unsigned long long)pending) - 1;
-    const int s = __shfl(slot, leader);
-    const unsigned long long m = __ballot(slot == s);
+    const int k = __shfl(key, leader);
+    const unsigned long long m = __ballot(key == k);
     int base = 0;
-    if (lane == leader) base = atomicAdd(&counters[s], (int)__popcll(m));
+    if (lane == leader) base = atomicAdd(&counters[k], (int)__popcll(m));
     base = __shfl(base, leader);
-    if (slot == s) rank = base + (int)__popcll(m & below);
+    if (key == k) ticket = base + (int)__popcll(m & below);
     pending &= ~m;
   }
-  return rank;
+  return ticket;
+}
+// counter of a particle's cell in a group's SCAT_CELL counters (the tile and
+// SORT_EVERY cells around it)
+__device__ inline int sort_cell(const Region& q, unsigned cw, bool& bad) {
+  const int sx = clampi(cell_ix(cw) - (q.T * TX - SORT_EVERY), 0, CR - 1, bad);
+  const int sr = clampi(cell_jr(cw) - (q.tcr * TR - SORT_EVERY), 0, CR - 1, bad);
+  return sx * CR + sr;
 }
 
 // SCAT: SCAT_NONE updates p in place and keeps the layout.  SCAT_TILE
@@ -558,12 +561,15 @@ __device__ inline int wave_slot_rank(int slot, int* counters) {
 // deposits' LDS atomics do not collide), at the price of strided writes.
 // O: particle shape order (1 linear, 2 quadratic; order 2 re-sorts every
 // second step, so its wider stencil stays inside the same halo).
-// Waves per SIMD the compiler must allow: the FP32 in-place pass fits four
-// work groups per CU in LDS (its smaller region, no staged gradient), so its
-// registers are held to 64 per lane (eight waves per SIMD); the others are
-// not constrained.
-template <class R, bool DEFER, int SCAT, int O> constexpr int mom_waves_per_simd() {
-  return (sizeof(R) == 4 && !DEFER && SCAT == SCAT_NONE) ? 8 : 1;
+// Waves per SIMD the compiler must allow.  FP32: the in-place pass fits four
+// work groups per CU in LDS (its smaller region, no staged gradient) and is
+// held to 64 registers per lane (eight waves per SIMD); a tile sort fits three
+// (80 registers), or eight waves with mode 0 alone.  FP64: two work groups in
+// place (128 registers), one in a sort.
+template <class R, bool M1, bool DEFER, int SCAT, int O> constexpr int mom_waves_per_simd() {
+  if (DEFER || SCAT == SCAT_CELL) return 1;
+  if (sizeof(R) == 8) return SCAT == SCAT_NONE ? 4 : 1;
+  return SCAT == SCAT_NONE || !M1 ? 8 : 6;
 }
 
 // Margin: a scattering pass gathers at most SORT_EVERY cells of drift from
@@ -571,7 +577,7 @@ template <class R, bool DEFER, int SCAT, int O> constexpr int mom_waves_per_simd
 // the passes in between have drifted one cell less and stage a region with
 // one cell less of margin (fewer bytes staged, less LDS per work group).
 template <class R, bool M1, bool DEFER, int SCAT, int O, bool NT>
-__global__ __launch_bounds__(WG, (mom_waves_per_simd<R, DEFER, SCAT, O>())) void k_momentum(
+__global__ __launch_bounds__(WG, (mom_waves_per_simd<R, M1, DEFER, SCAT, O>())) void k_momentum(
     Geo g, Grids<R> f, R* __restrict__ chi_out,
                                                  Parts<R> src, Parts<R> dst, Layout Ls, Layout Ld,
                                                  int* __restrict__ ccur, R* __restrict__ gscr,
@@ -579,11 +585,10 @@ __global__ __launch_bounds__(WG, (mom_waves_per_simd<R, DEFER, SCAT, O>())) void
   using C = typename cplx_of<R>::type;
   constexpr int H = (SCAT == SCAT_NONE && !DEFER) ? HALO - 1 : HALO;
   constexpr int RX = Halo<H>::X, RL = Halo<H>::R, RN = Halo<H>::N;
-  __shared__ SmemMom<R, M1, H, O, SCAT != SCAT_NONE> sm;
+  __shared__ SmemMom<R, M1, H, O, SCAT != SCAT_NONE, SCAT == SCAT_CELL> sm;
   const int item = item_of(blockIdx.x, gridDim.x);
   if (item >= *Ls.n_items) return;
   const int4 it = Ls.items[item];
-  const int start = it.y, count = it.z;
   const Region q = region_of(g, it.x, H);
   const R hdt = (R)(0.5 * g.dt);
 
@@ -614,23 +619,25 @@ __global__ __launch_bounds__(WG, (mom_waves_per_simd<R, DEFER, SCAT, O>())) void
     sm.phi[k] = (px && pv) ? (R)0.5 * cnorm(venv) : (R)0;
     sm.chi[k] = 0;
     if (M1) {
-      const C z = mk<C>((R)0, (R)0);
+      // (selected by component: a select of whole pairs goes through scratch
+      // memory on the FP64 path)
+      auto scaled = [](bool ok, C v, R by) { return mk<C>(ok ? v.x * by : (R)0, ok ? v.y * by : (R)0); };
       const C e1 = f.ex1[in], r1 = f.er1[ih], t1 = f.et1[in];
       const C bx = f.bxb1[ih], br = f.brb1[in], bt = f.btb1[ih];
-      sm.ex1[k] = (dxok && pv) ? (pg ? cscale(e1, (R)-1) : e1) : z;
-      sm.er1[k] = px ? cscale(r1, hp) : z;
-      sm.et1[k] = (px && pv) ? t1 : z;
-      sm.bx1[k] = px ? cscale(bx, hs) : z;
-      sm.br1[k] = (dxok && pv) ? br : z;
-      sm.bt1[k] = dxok ? cscale(bt, hp) : z;
+      sm.ex1[k] = scaled(dxok && pv, e1, pg ? (R)-1 : (R)1);
+      sm.er1[k] = scaled(px, r1, hp);
+      sm.et1[k] = scaled(px && pv, t1, (R)1);
+      sm.bx1[k] = scaled(px, bx, hs);
+      sm.br1[k] = scaled(dxok && pv, br, (R)1);
+      sm.bt1[k] = scaled(dxok, bt, hp);
     }
   }
   for (int k = threadIdx.x; k < RL; k += WG) {
     const int j = q.R0 + k;
     sm.ivol[k] = (j >= 0 && j <= g.nr) ? inv_vol_node<R>(g, j) : (R)0;
   }
-  if (SCAT != SCAT_NONE)
-    for (int k = threadIdx.x; k < (SCAT == SCAT_CELL ? CRN : 9); k += WG) sm.ccell[k] = 0;
+  if (SCAT == SCAT_CELL)
+    for (int k = threadIdx.x; k < CRN; k += WG) sm.ccell[k] = 0;
   __syncthreads();
   // grad Phi by centred differences on the primal nodes (zero radial
   // derivative on the axis, odd below it).  A scattering pass with quadratic
@@ -653,140 +660,14 @@ __global__ __launch_bounds__(WG, (mom_waves_per_simd<R, DEFER, SCAT, O>())) void
     }
   }
 
-  // ---- destination (tile of the 3 x 3 neighbourhood, or cell) and rank
-  // of each particle, kept in registers (the loops over a thread's
-  // particles are unrolled).  Without the scatter only the live flag is kept.
-  // An incremental tile sort ranks the particles that change tile only.
-  const bool move = SCAT == SCAT_TILE && *Ld.mode == LAYOUT_MOVE;
-  // a cell sort whose copy is gathered afterwards (k_permute)
-  const bool gather = SCAT == SCAT_CELL && !DEFER && (*Ld.mode & LAYOUT_GATHER) != 0;
-  // the particles of an item past the segments all join their tiles' segments
-  const bool fill_item = start >= Ls.offsets[g.ntiles];
-  constexpr int STAY = 1 << 30;  // slot_rank of a particle that keeps its slot
-  int slot_rank[PPT];
-  bool bad = false;
-#pragma unroll
-  for (int u = 0; u < PPT; ++u) {
-    const int k = threadIdx.x + u * WG;
-    slot_rank[u] = -1;
-    int tslot = -1;  // SCAT_TILE: destination tile of the 3 x 3 neighbourhood
-    if (k < count) {
-      const unsigned cw = *elem(src.cell, start + k);
-      if (cw != kDead) {
-        if (SCAT == SCAT_TILE) {
-          const int dtx = clampi(cell_ix(cw) / TX - q.T, -1, 1, bad);
-          const int dtr = clampi(cell_jr(cw) / TR - q.tcr, -1, 1, bad);
-          tslot = (dtx + 1) * 3 + (dtr + 1);
-          if (move && tslot == 4 && !fill_item) {
-            slot_rank[u] = STAY;
-            tslot = -1;
-          }
-        } else if (SCAT == SCAT_CELL) {
-          const int sx = clampi(cell_ix(cw) - (q.T * TX - SORT_EVERY), 0, CR - 1, bad);
-          const int sr = clampi(cell_jr(cw) - (q.tcr * TR - SORT_EVERY), 0, CR - 1, bad);
-          const int slot = sx * CR + sr;
-          slot_rank[u] = (slot << 16) | atomicAdd(&sm.ccell[slot], 1);
-        } else {
-          slot_rank[u] = 0;
-        }
-      }
-    }
-    if (SCAT == SCAT_TILE) {  // the loop is wavefront-uniform (PPT iterations)
-      const int r = wave_slot_rank(tslot, sm.ccell);
-      if (tslot >= 0) slot_rank[u] = (tslot << 16) | r;
-    }
-  }
-  __syncthreads();
-  // one reservation per destination tile, or per destination cell (its
-  // slots in cell order).  An incremental sort reserves arrival tickets and
-  // keeps, per destination, where its free slots and overflow range start
-  // and how many each holds.
-  if (SCAT == SCAT_TILE) {
-    if (threadIdx.x < 9) {
-      const int c = sm.ccell[threadIdx.x];
-      if (c > 0) {
-        int tx2 = q.tcx + threadIdx.x / 3 - 1;
-        if (tx2 < 0) tx2 += g.ntxa;
-        if (tx2 >= g.ntxa) tx2 -= g.ntxa;
-        const int tr2 = q.tcr + threadIdx.x % 3 - 1;
-        const int key = tx2 * g.ntr + tr2;
-        if (tr2 < 0 || tr2 >= g.ntr) {
-          sm.ccell[threadIdx.x] = -1;  // no cell lies there: its particles are flagged, not written
-        } else {
-          sm.ccell[threadIdx.x] = atomicAdd(&Ld.cursor[key], c);
-        }
-        if (move && sm.ccell[threadIdx.x] >= 0) {
-          int* pl = &sm.ccell[9 + 4 * threadIdx.x];
-          pl[0] = Ls.offsets[key] + Ls.ext[key];
-          pl[1] = Ld.ext[key] - Ls.ext[key];
-          pl[2] = Ld.ovb[key];
-          pl[3] = Ld.ovn[key];
-        }
-      }
-    }
-    __syncthreads();
-  }
-  if (SCAT == SCAT_CELL) {
-    for (int k = threadIdx.x; k < CRN; k += WG) {
-      const int c = sm.ccell[k];
-      if (c > 0) {
-        const int rel = (int)((long long)q.T * TX - SORT_EVERY + k / CR - g.shift);
-        const int j = q.tcr * TR - SORT_EVERY + k % CR;
-        sm.ccell[k] = atomicAdd(&ccur[(size_t)phys_col(g, rel) * g.pitch + j], c);
-      }
-    }
-    __syncthreads();
-  }
-
-  // ---- gather, push, deposit, scatter
-  bool lost = false;
-#pragma unroll
-  for (int u = 0; u < PPT; ++u) {
-    if (slot_rank[u] < 0) continue;
-    const int p = start + threadIdx.x + u * WG;
-    const unsigned cw = pld<NT>(elem(src.cell, p));  // its second read (the first above)
-    int d = p;
-    const bool stay = SCAT == SCAT_TILE && slot_rank[u] == STAY;
-    if (SCAT == SCAT_TILE && !stay) {
-      const int sl = slot_rank[u] >> 16;
-      if (sm.ccell[sl] < 0) {
-        bad = true;
-        continue;
-      }
-      const int tk = sm.ccell[sl] + (slot_rank[u] & 0xFFFF);
-      d = tk;
-      if (move) {
-        // ticket tk of the destination: its free slots, then its overflow
-        const int* pl = &sm.ccell[9 + 4 * sl];
-        d = tk < pl[1] ? pl[0] + tk : (tk - pl[1] < pl[3] ? pl[2] + tk - pl[1] : -1);
-        if (d < 0) {  // more arrivals than the scan counted: never written
-          lost = true;
-          continue;
-        }
-      }
-      if ((long long)d >= g.cap) {  // the scan has flagged the overflow
-        bad = true;
-        continue;
-      }
-    }
-    if (SCAT == SCAT_CELL) {
-      // rank in the destination tile's cell order, then the transposed
-      // placement inside its work item (as at loading)
-      const int r = sm.ccell[slot_rank[u] >> 16] + (slot_rank[u] & 0xFFFF);
-      const int key = tile_key(g, cell_ix(cw), cell_jr(cw));
-      const int off = Ld.offsets[key], v = Ld.ext[key];
-      if (r >= v) {  // counts and particles disagree: flagged, never written
-        bad = true;
-        continue;
-      }
-      d = off + placed_rank<O>(r, v, g.chunk);
-      if ((long long)d >= g.cap) {  // the scan has flagged the overflow
-        bad = true;
-        continue;
-      }
-    }
-    const R fx = pld<NT>(elem(src.fx, p)), fr = pld<NT>(elem(src.fr, p)), th = pld<NT>(elem(src.th, p)), w = pld<NT>(elem(src.w, p));
-    R pv[3] = {pld<NT>(elem(src.px, p)), pld<NT>(elem(src.py, p)), pld<NT>(elem(src.pz, p))};
+  bool bad = false, lost = false;
+  // the particles of the item: its range and, for the last item of a tile,
+  // the tile's overflow range riding with it
+  const int total = it.z + it.w, ov_base = (it.w > 0 ? Ls.ovb[it.x] : 0) - it.z;
+  auto slot_of = [&](int k) { return k + (k < it.z ? it.y : ov_base); };
+  // gather, push and chi deposit of one particle (p updated); d: the slot of
+  // a deferred deposit
+  auto push = [&](unsigned cw, R fx, R fr, R th, R w, R(&pv)[3], int d) {
     // the cell relative to the region: [1, RX - 3] for the linear stencils
     // (and the differences of Phi one node further out); order 2 keeps
     // [2, RX - 4], the range its position pass needs for the current
@@ -894,31 +775,129 @@ __global__ __launch_bounds__(WG, (mom_waves_per_simd<R, DEFER, SCAT, O>())) void
           Acc0<R>::add_prod(&sm.chi[(Px.i + aa) * RL + Pr.i + bb], wa, (double)(bb ? Pr.b : Pr.a));
       }
     }
-    if (gather) {
-      // the cell-ordered copy is gathered afterwards (k_permute): p is
-      // updated in place and the destination slot records where it comes from
-      pst<NT>(elem(src.px, p), pv[0]);
-      pst<NT>(elem(src.py, p), pv[1]);
-      pst<NT>(elem(src.pz, p), pv[2]);
-      *elem(inv, d) = (unsigned)p;
-    } else if (SCAT != SCAT_NONE && !stay) {
-      // an incremental sort writes within the same buffer, into slots no
-      // work item of this pass reads (free or overflow slots)
-      const Parts<R>& out = move ? src : dst;
-      pst<NT>(elem(out.cell, d), cw);
-      pst<NT>(elem(out.fx, d), fx);
-      pst<NT>(elem(out.fr, d), fr);
-      pst<NT>(elem(out.th, d), th);
-      pst<NT>(elem(out.px, d), pv[0]);
-      pst<NT>(elem(out.py, d), pv[1]);
-      pst<NT>(elem(out.pz, d), pv[2]);
-      pst<NT>(elem(out.w, d), w);
-      pst<NT>(elem(out.id, d), pld<NT>(elem(src.id, p)));
-      if (move && !fill_item) *elem(src.cell, p) = kDead;  // its old slot
-    } else {
-      pst<NT>(elem(src.px, p), pv[0]);
-      pst<NT>(elem(src.py, p), pv[1]);
-      pst<NT>(elem(src.pz, p), pv[2]);
+  };
+
+  // a tile sort that moves only the particles that change tile
+  const bool move = SCAT == SCAT_TILE && *Ld.mode == LAYOUT_MOVE;
+  // a cell sort whose copy is gathered afterwards (k_permute)
+  const bool gather = SCAT == SCAT_CELL && !DEFER && (*Ld.mode & LAYOUT_GATHER) != 0;
+  if constexpr (SCAT == SCAT_CELL) {
+    // particles per destination cell, then one reservation per cell: each
+    // counter becomes the first rank of the group's particles in its cell
+    // (the loop below hands the ranks out)
+    for (int k = threadIdx.x; k < total; k += WG) {
+      const unsigned cw = *elem(src.cell, slot_of(k));
+      if (cw != kDead) atomicAdd(&sm.ccell[sort_cell(q, cw, bad)], 1);
+    }
+    __syncthreads();
+    for (int k = threadIdx.x; k < CRN; k += WG) {
+      const int c = sm.ccell[k];
+      if (c > 0) {
+        const int rel = (int)((long long)q.T * TX - SORT_EVERY + k / CR - g.shift);
+        const int j = q.tcr * TR - SORT_EVERY + k % CR;
+        sm.ccell[k] = atomicAdd(&ccur[(size_t)phys_col(g, rel) * g.pitch + j], c);
+      }
+    }
+  }
+  if (SCAT == SCAT_CELL || (O == 2 && SCAT != SCAT_NONE)) __syncthreads();
+  const int seg_end = SCAT == SCAT_TILE ? Ls.offsets[g.ntiles] : 0;
+
+  // ---- gather, push, deposit, scatter
+  {
+    // (SCAT_TILE ranks over whole wavefronts: uniform trip count)
+    const int trips = SCAT == SCAT_TILE ? (total + 63) & ~63 : total;
+    for (int k = threadIdx.x; k < trips; k += WG) {
+      const bool valid = SCAT != SCAT_TILE || k < total;
+      const int p = slot_of(valid ? k : 0);
+      const unsigned cw = pld<NT>(elem(src.cell, p));
+      const R fx = pld<NT>(elem(src.fx, p)), fr = pld<NT>(elem(src.fr, p)), th = pld<NT>(elem(src.th, p)), w = pld<NT>(elem(src.w, p));
+      R pv[3] = {pld<NT>(elem(src.px, p)), pld<NT>(elem(src.py, p)), pld<NT>(elem(src.pz, p))};
+      bool live = valid && cw != kDead;
+      int d = p;
+      bool stay = true;
+      if constexpr (SCAT == SCAT_TILE) {
+        // The particle's slot in the new layout, unless it keeps its own: it
+        // does when an incremental sort finds it in its tile's segment and
+        // still in that tile (nearly all).  The others take tickets, one
+        // global atomic per destination tile in a wavefront.
+        int key = -1;
+        if (live) {
+          const int tx = cell_ix(cw) - q.T * TX, tr = cell_jr(cw) - q.tcr * TR;
+          const bool same = (unsigned)tx < (unsigned)TX && (unsigned)tr < (unsigned)TR;
+          if (!same || !move || p >= seg_end) {
+            int tx2 = q.tcx + clampi((tx + TX) / TX - 1, -1, 1, bad);
+            if (tx2 < 0) tx2 += g.ntxa;
+            if (tx2 >= g.ntxa) tx2 -= g.ntxa;
+            const int tr2 = q.tcr + clampi((tr + TR) / TR - 1, -1, 1, bad);
+            stay = false;
+            if (tr2 < 0 || tr2 >= g.ntr) {
+              bad = true;  // no cell lies there: flagged, not written
+              live = false;
+            } else {
+              key = tx2 * g.ntr + tr2;
+            }
+          }
+        }
+        if (__ballot(key >= 0)) {
+          const int tk = wave_ticket(key, Ld.cursor);
+          if (key >= 0) {
+            d = tk;
+            if (move) {
+              // ticket tk of the destination: its free slots, then its overflow
+              const int e = Ls.ext[key], room = Ld.ext[key] - e;
+              d = tk < room ? Ls.offsets[key] + e + tk : (tk - room < Ld.ovn[key] ? Ld.ovb[key] + tk - room : -1);
+            }
+            if (d < 0) {  // more arrivals than the scan counted: never written
+              lost = true;
+              live = false;
+            } else if ((long long)d >= g.cap) {  // the scan has flagged the overflow
+              bad = true;
+              live = false;
+            }
+          }
+        }
+      }
+      if (!live) continue;
+      if constexpr (SCAT == SCAT_CELL) {
+        // rank in the destination tile's cell order, then the transposed
+        // placement inside its work item (as at loading)
+        const int r = atomicAdd(&sm.ccell[sort_cell(q, cw, bad)], 1);
+        const int key = tile_key(g, cell_ix(cw), cell_jr(cw));
+        const int off = Ld.offsets[key], v = Ld.ext[key];
+        if (r >= v) {  // counts and particles disagree: flagged, never written
+          bad = true;
+          continue;
+        }
+        d = off + placed_rank<O>(r, v, g.chunk);
+        if ((long long)d >= g.cap) {  // the scan has flagged the overflow
+          bad = true;
+          continue;
+        }
+        stay = gather;
+      }
+      push(cw, fx, fr, th, w, pv, d);
+      if (SCAT == SCAT_NONE || stay) {
+        pst<NT>(elem(src.px, p), pv[0]);
+        pst<NT>(elem(src.py, p), pv[1]);
+        pst<NT>(elem(src.pz, p), pv[2]);
+        // the cell-ordered copy is gathered afterwards (k_permute): the
+        // destination slot records where it comes from
+        if (SCAT == SCAT_CELL) *elem(inv, d) = (unsigned)p;
+      } else {
+        // an incremental sort writes within the same buffer, into slots no
+        // work item of this pass reads (free or overflow slots)
+        const Parts<R>& out = move ? src : dst;
+        pst<NT>(elem(out.cell, d), cw);
+        pst<NT>(elem(out.fx, d), fx);
+        pst<NT>(elem(out.fr, d), fr);
+        pst<NT>(elem(out.th, d), th);
+        pst<NT>(elem(out.px, d), pv[0]);
+        pst<NT>(elem(out.py, d), pv[1]);
+        pst<NT>(elem(out.pz, d), pv[2]);
+        pst<NT>(elem(out.w, d), w);
+        pst<NT>(elem(out.id, d), pld<NT>(elem(src.id, p)));
+        if (move && p < seg_end) *elem(src.cell, p) = kDead;  // its old slot
+      }
     }
   }
   if (bad) atomicOr(err, ERR_HALO);
@@ -1384,12 +1363,12 @@ __device__ inline void flush_cells(const int* cc, const Region& q, const Geo& g,
 
 // The per-tile counts of a work item, t[d] for d = 3 (dx + 1) + (dr + 1)
 // the particles that moved to the neighbouring tile (dx, dr) (counted
-// before a tile sort), t[9] the particles removed, t[10] the live ones at
-// the start of a fill item.  hist (particles per tile, kept current from
-// step to step) loses the removed and moved ones and gains the moved ones
-// at their new tiles; before a tile sort, arr gains the moved ones, and
-// every particle of a fill item that stays in its tile.
-__device__ inline void flush_tiles(const int* t, const Region& q, const Geo& g, const SortCounts& sc, bool fill_item) {
+// before a tile sort), t[9] the particles removed, t[10] those of a range
+// past the segments that stay in the tile (before a tile sort).  hist
+// (particles per tile, kept current from step to step) loses the removed and
+// moved ones and gains the moved ones at their new tiles; before a tile sort,
+// arr gains the moved ones, and those that stay past the segments.
+__device__ inline void flush_tiles(const int* t, const Region& q, const Geo& g, const SortCounts& sc) {
   if (threadIdx.x >= 9) return;
   const int d = threadIdx.x;
   int v = t[d];
@@ -1398,10 +1377,7 @@ __device__ inline void flush_tiles(const int* t, const Region& q, const Geo& g, 
     for (int e = 0; e < 9; ++e) moved += e == 4 ? 0 : t[e];
     const int key = q.tcx * g.ntr + q.tcr;
     if (t[9] + moved != 0) atomicAdd(&sc.hist[key], -(t[9] + moved));
-    if (sc.mode == SCAT_TILE && fill_item) {
-      const int stay = t[10] - t[9] - moved;
-      if (stay != 0) atomicAdd(&sc.arr[key], stay);
-    }
+    if (t[10] != 0) atomicAdd(&sc.arr[key], t[10]);
     return;
   }
   if (v == 0) return;
@@ -1534,13 +1510,15 @@ __device__ void inject_block(const InjectArgs& ia, Parts<R> P, const Layout& L, 
 // vacate: 1 when the window moves after this step (particles whose new
 // column is the window's first one are dropped after depositing); sc: what
 // to count for a sort at the next step (SortCounts)
-// The FP32 quadratic pass is held to six waves per SIMD (80 registers per
-// lane, the count the LDS allows), at the price of 12 bytes of spills per
-// lane.
-template <class R, int O> constexpr int pos_waves_per_simd() { return sizeof(R) == 8 ? 4 : (O == 2 ? 6 : 1); }
+// Registers are held to what the LDS allows in flight: three work groups per
+// CU with mode 1 (80 registers per lane, with some bytes of spills for the
+// quadratic shapes), more with mode 0 alone; FP64: two groups (128).
+template <class R, bool M1, int O> constexpr int pos_waves_per_simd() {
+  return sizeof(R) == 8 ? 4 : (M1 || O == 2) ? 6 : 8;
+}
 
 template <class R, bool M1, bool DEFER, int O, bool NT>
-__global__ __launch_bounds__(WG, (pos_waves_per_simd<R, O>())) void k_position(Geo g, Grids<R> f, R* __restrict__ jx_out,
+__global__ __launch_bounds__(WG, (pos_waves_per_simd<R, M1, O>())) void k_position(Geo g, Grids<R> f, R* __restrict__ jx_out,
                                                  R* __restrict__ jr_out,
                                                  typename cplx_of<R>::type* __restrict__ jx1_out,
                                                  typename cplx_of<R>::type* __restrict__ jr1_out,
@@ -1561,7 +1539,6 @@ __global__ __launch_bounds__(WG, (pos_waves_per_simd<R, O>())) void k_position(G
   const int item = item_of(blockIdx.x, item_blocks);
   if (item >= *L.n_items) return;
   const int4 it = L.items[item];
-  const int start = it.y, count = it.z;
   const Region q = region_of(g, it.x);
 
   // Phi^{n+1/2} = (|A^{n+1}|^2 + |A^n|^2)/4 on the primal nodes (order 2:
@@ -1580,18 +1557,7 @@ __global__ __launch_bounds__(WG, (pos_waves_per_simd<R, O>())) void k_position(G
   stage_pos_constants(sm, q, g);
   zero_pos_acc(sm);
   __syncthreads();
-  // Before a tile sort, the particles of an item past the tiles' segments
-  // (an injected column, an overflow range) all join their tiles'
-  // segments: their live count, taken before the pass removes any
-  const bool fill_item = start >= L.offsets[g.ntiles];
-  if (sc.mode == SCAT_TILE && fill_item) {
-    int c = 0;
-    for (int k = threadIdx.x; k < count; k += WG) c += P.cell[start + k] != kDead ? 1 : 0;
-    c = wave_sum_i(c);
-    if (__lane_id() == 0 && c != 0) atomicAdd(&sm.tcnt[10], c);
-    __syncthreads();
-  }
-
+  const int seg_end = L.offsets[g.ntiles];
   bool bad = false;
   // the next particle's record is loaded before this one is processed
   // (the stores below would otherwise keep the loads from moving up)
@@ -1599,9 +1565,8 @@ __global__ __launch_bounds__(WG, (pos_waves_per_simd<R, O>())) void k_position(G
     unsigned cw;
     R fx, fr, th, w, px, py, pz;
   };
-  auto fetch = [&](int k) {
+  auto fetch = [&](int p) {
     Rec r;
-    const int p = start + k;
     r.cw = pld<NT>(elem(P.cell, p));
     r.fx = pld<NT>(elem(P.fx, p));
     r.fr = pld<NT>(elem(P.fr, p));
@@ -1612,12 +1577,15 @@ __global__ __launch_bounds__(WG, (pos_waves_per_simd<R, O>())) void k_position(G
     r.pz = pld<NT>(elem(P.pz, p));
     return r;
   };
+  // the item's range, then the overflow range riding with it
+  const int total = it.z + it.w, ov_base = (it.w > 0 ? L.ovb[it.x] : 0) - it.z;
+  auto slot_of = [&](int k) { return k + (k < it.z ? it.y : ov_base); };
   Rec nxt;
-  if (threadIdx.x < count) nxt = fetch(threadIdx.x);
-  for (int k = threadIdx.x; k < count; k += WG) {
+  if (threadIdx.x < total) nxt = fetch(slot_of(threadIdx.x));
+  for (int k = threadIdx.x; k < total; k += WG) {
     const Rec cur = nxt;
-    if (k + WG < count) nxt = fetch(k + WG);
-    const int p = start + k;
+    const int p = slot_of(k);
+    if (k + WG < total) nxt = fetch(slot_of(k + WG));
     const unsigned cw = cur.cw;
     if (cw == kDead) continue;
     const R fx = cur.fx, fr = cur.fr, th = cur.th, w = cur.w;
@@ -1679,6 +1647,10 @@ __global__ __launch_bounds__(WG, (pos_waves_per_simd<R, O>())) void k_position(G
         const int dtx = clampi((tx + TX) / TX - 1, -1, 1, bad);
         const int dtr = clampi((tr + TR) / TR - 1, -1, 1, bad);
         atomicAdd(&sm.tcnt[(dtx + 1) * 3 + dtr + 1], 1);
+      } else if (p >= seg_end) {
+        // past the segments (an injected column, an overflow range): it joins
+        // its tile's segment
+        atomicAdd(&sm.tcnt[10], 1);
       }
     }
   }
@@ -1686,7 +1658,7 @@ __global__ __launch_bounds__(WG, (pos_waves_per_simd<R, O>())) void k_position(G
   __syncthreads();
   if (!DEFER) flush_current<R, M1, O>(sm, q, g, jx_out, jr_out, jx1_out, jr1_out, jt1_out);
   if (sc.mode == SCAT_CELL) flush_cells(sm.ccell, q, g, sc.ccount);
-  flush_tiles(sm.tcnt, q, g, sc, fill_item);
+  flush_tiles(sm.tcnt, q, g, sc);
 }
 
 // ============================= deferred deposits (stage-by-stage API) ==
@@ -1707,8 +1679,8 @@ __global__ __launch_bounds__(WG) void k_deposit_chi(Geo g, R* __restrict__ chi_o
   }
   __syncthreads();
   bool bad = false;
-  for (int k = threadIdx.x; k < it.z; k += WG) {
-    const int p = it.y + k;
+  for (int k = threadIdx.x; k < it.z + it.w; k += WG) {
+    const int p = item_slot(L, it, k);
     const unsigned cw = P.cell[p];
     if (cw == kDead) continue;
     const int a = clampi(cell_ix(cw) - q.X0, 0, LX - 2, bad);
@@ -1749,8 +1721,8 @@ __global__ __launch_bounds__(WG) void k_deposit_J(Geo g, R* __restrict__ jx_out,
   zero_pos_acc(sm);
   __syncthreads();
   bool bad = false;
-  for (int k = threadIdx.x; k < it.z; k += WG) {
-    const int p = it.y + k;
+  for (int k = threadIdx.x; k < it.z + it.w; k += WG) {
+    const int p = item_slot(L, it, k);
     const unsigned cw = P.cell[p];
     if (cw == kDead) continue;
     const R gm = scr.w[p];

@@ -76,7 +76,7 @@ template <int NT> __device__ inline int block_scan(int v, int* s_w, int* total) 
 __device__ inline void bump_pending(const Geo& g, Layout L, int* pending) {
   const int np = pending[0];
   if (np == 0) return;
-  const int n0 = *L.n_items, seg_end = L.offsets[g.ntiles];
+  const int n0 = *L.n_items, seg_end = L.offsets[g.ntiles];  // (an injected item has no riders)
   for (int i = threadIdx.x; i < np; i += blockDim.x) {
     const int4 it = L.items[n0 + i];
     if (it.y < seg_end) L.ext[it.x] += it.z;
@@ -104,6 +104,10 @@ __device__ inline int emit_items(const Geo& g, int4* items, int em, int max_em, 
   }
   return nm;
 }
+
+// whether the v particles of a tile's overflow range ride with the last work
+// item of the n in its segment
+__device__ inline bool overflow_rides(const Geo& g, int n, int v) { return n > 0 && v > 0 && v <= min(MAX_RIDERS, g.chunk / 2); }
 
 // Slots a rebuilt layout holds for tile t of v particles: v, or a full tile
 // when the tile lies in the `entering` tile columns ahead of a moving window
@@ -210,7 +214,8 @@ __device__ inline void move_layout(const Geo& g, int* hist, int* arr, Layout in,
     const int a = arr[t], e = in.ext[t], cap = in.offsets[t + 1] - in.offsets[t];
     const int tail = min(a, cap - e);
     ov += a - tail;
-    m += (e + tail + g.chunk - 1) / g.chunk + (a - tail + g.chunk - 1) / g.chunk;
+    m += (e + tail + g.chunk - 1) / g.chunk;
+    if (!overflow_rides(g, e + tail, a - tail)) m += (a - tail + g.chunk - 1) / g.chunk;
   }
   int total_ov = 0, n_items = 0;
   const int ov_pre = block_scan<NT>(ov, s_w, &total_ov);
@@ -235,7 +240,11 @@ __device__ inline void move_layout(const Geo& g, int* hist, int* arr, Layout in,
     out.ovb[t] = ob;
     out.ovn[t] = a - tail;
     em += emit_items(g, out.items, em, item_cap, t, base, e + tail, capacity);
-    em += emit_items(g, out.items, em, item_cap, t, ob, a - tail, capacity);
+    if (overflow_rides(g, e + tail, a - tail)) {
+      if (em <= item_cap) out.items[em - 1].w = a - tail;
+    } else {
+      em += emit_items(g, out.items, em, item_cap, t, ob, a - tail, capacity);
+    }
     ob += a - tail;
     arr[t] = 0;
   }

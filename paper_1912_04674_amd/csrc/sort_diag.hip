@@ -62,8 +62,8 @@ __global__ __launch_bounds__(DG) void k_diag_particles(Geo g, Parts<R> P, Layout
   const int n_items = *L.n_items;
   for (int item = blockIdx.x; item < n_items; item += DIAG_BLOCKS) {
     const int4 it = L.items[item];
-    for (int k = threadIdx.x; k < it.z; k += DG) {
-      const int p = it.y + k;
+    for (int k = threadIdx.x; k < it.z + it.w; k += DG) {
+      const int p = item_slot(L, it, k);
       const unsigned cw = P.cell[p];
       if (cw == kDead) continue;
       const double w = P.w[p], px = P.px[p], py = P.py[p], pz = P.pz[p];
