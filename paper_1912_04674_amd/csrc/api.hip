@@ -530,6 +530,14 @@ template <class R> struct SimT : envpic_sim {
     g.rdx = 1.0 / p.dx;
     g.rdr = 1.0 / p.dr;
     g.dtdx = p.dt / p.dx;
+    g.dt_f = (float)g.dt;
+    g.dr_f = (float)g.dr;
+    g.rdr_f = (float)g.rdr;
+    g.dtdx_f = (float)g.dtdx;
+    g.hdt_f = (float)(0.5 * g.dt);
+    g.hrdx_f = (float)(0.5 * g.rdx);
+    g.hrdr_f = (float)(0.5 * g.rdr);
+    g.hdtdx_f = (float)(0.5 * g.dtdx);
     g.chunk = sz.chunk;
     g.order = p.shape_order == 2 ? 2 : 1;
     // one buffer's records: cell word and id, six reals and the weight

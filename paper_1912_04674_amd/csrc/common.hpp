@@ -121,6 +121,8 @@ struct Geo {
   long long cap;     // particle slots per buffer
   double dx, dr, dt;
   double rdx, rdr, dtdx;  // 1 / dx, 1 / dr, dt / dx
+  float dt_f, dr_f, rdr_f, dtdx_f;               // the same in FP32
+  float hdt_f, hrdx_f, hrdr_f, hdtdx_f;          // and half of them
   float fix;         // fixed-point scale of the FP32 path's mode-1 current sums
   double unfix;      // 1 / fix
   float fix0;        // fixed-point scale of the FP32 path's chi and mode-0 current sums

@@ -44,6 +44,13 @@ __device__ inline int floor_int(float x) {
 __device__ inline int floor_int(double x) { return (int)floor(x); }
 __device__ inline float fract_r(float x) { return __builtin_amdgcn_fractf(x); }
 __device__ inline double fract_r(double x) { return __builtin_amdgcn_fract(x); }
+// a constant in the type of the path (the FP32 copy comes in as a kernel
+// argument, which stays in a scalar register; one converted on the device
+// would take a vector register)
+template <class R> __device__ inline R pick(double x, float xf) {
+  if constexpr (sizeof(R) == 4) return xf;
+  else return x;
+}
 // x clamped to [lo, hi]; a NaN gives lo
 __device__ inline float clamp_r(float x, float lo, float hi) { return __builtin_amdgcn_fmed3f(x, lo, hi); }
 __device__ inline double clamp_r(double x, double lo, double hi) { return fmin(fmax(x, lo), hi); }
@@ -56,6 +63,11 @@ template <class R> __device__ inline Lin<R> dual_w(int c, R f) {
 template <class R, int RL = LR> __device__ inline R interp2(const R* a, Lin<R> sx, Lin<R> sr) {
   return sx.a * (sr.a * a[sx.i * RL + sr.i] + sr.b * a[sx.i * RL + sr.i + 1]) +
          sx.b * (sr.a * a[(sx.i + 1) * RL + sr.i] + sr.b * a[(sx.i + 1) * RL + sr.i + 1]);
+}
+// the same from the four weight products
+template <class R, int RL = LR> __device__ inline R interp2w(const R* a, Lin<R> sx, Lin<R> sr) {
+  const R* n = &a[sx.i * RL + sr.i];
+  return sx.a * sr.a * n[0] + sx.a * sr.b * n[1] + sx.b * sr.a * n[RL] + sx.b * sr.b * n[RL + 1];
 }
 template <class C, class R, int RL = LR> __device__ inline C interp2c(const C* a, Lin<R> sx, Lin<R> sr) {
   C v00 = a[sx.i * RL + sr.i], v01 = a[sx.i * RL + sr.i + 1];
@@ -590,7 +602,7 @@ __global__ __launch_bounds__(WG, (mom_waves_per_simd<R, M1, DEFER, SCAT, O>())) 
   if (item >= *Ls.n_items) return;
   const int4 it = Ls.items[item];
   const Region q = region_of(g, it.x, H);
-  const R hdt = (R)(0.5 * g.dt);
+  const R hdt = pick<R>(0.5 * g.dt, g.hdt_f);
 
   // ---- stage E, Bbar, Phi (and mode 1) of the region in LDS.  Every load
   // reads a valid address (the index falls back to the column start) and the
@@ -643,7 +655,7 @@ __global__ __launch_bounds__(WG, (mom_waves_per_simd<R, M1, DEFER, SCAT, O>())) 
   // derivative on the axis, odd below it).  A scattering pass with quadratic
   // shapes stages it (the outermost ring of the region is unused); the
   // other gathers form it from the staged Phi (below).
-  const R i2dx = (R)(0.5 * g.rdx), i2dr = (R)(0.5 * g.rdr);
+  const R i2dx = pick<R>(0.5 * g.rdx, g.hrdx_f), i2dr = pick<R>(0.5 * g.rdr, g.hrdr_f);
   if constexpr (O == 2 && SCAT != SCAT_NONE) {
     for (int k = threadIdx.x; k < RN; k += WG) {
       const int a = k / RL, b = k - (k / RL) * RL;
@@ -704,23 +716,31 @@ __global__ __launch_bounds__(WG, (mom_waves_per_simd<R, M1, DEFER, SCAT, O>())) 
     } else {
       Px = primal_w<R>(a, fx);
       Pr = primal_w<R>(b, fr);
-      const Lin<R> Dx = dual_w<R>(a, fx), Dr = dual_w<R>(b, fr);
-      ex = interp2<R, RL>(sm.ex, Dx, Pr);
-      er = interp2<R, RL>(sm.er, Px, Dr);
-      bt = interp2<R, RL>(sm.bt, Dx, Dr);
-      // Phi on the 4 x 4 nodes around the cell (corners unused): itself on
-      // the inner 2 x 2, its centred differences at those four nodes (the
-      // radial one zero on the axis row)
+      // Phi on the 4 x 4 nodes around the cell (corners unused): interpolated
+      // along r on the four columns, whose differences interpolated along x
+      // give the x derivative, and along x on the four rows (the radial
+      // difference at the axis row is zero)
       const R* pc = &sm.phi[a * RL + b];
       const R p00 = pc[0], p01 = pc[1], p10 = pc[RL], p11 = pc[RL + 1];
-      ph = Px.a * (Pr.a * p00 + Pr.b * p01) + Px.b * (Pr.a * p10 + Pr.b * p11);
-      const R gx00 = (p10 - pc[-RL]) * i2dx, gx01 = (p11 - pc[1 - RL]) * i2dx;
-      const R gx10 = (pc[2 * RL] - p00) * i2dx, gx11 = (pc[2 * RL + 1] - p01) * i2dx;
-      gx = Px.a * (Pr.a * gx00 + Pr.b * gx01) + Px.b * (Pr.a * gx10 + Pr.b * gx11);
-      const bool axis = q.R0 + b == 0;
-      const R gr00 = axis ? (R)0 : (p01 - pc[-1]) * i2dr, gr10 = axis ? (R)0 : (p11 - pc[RL - 1]) * i2dr;
-      const R gr01 = (pc[2] - p00) * i2dr, gr11 = (pc[RL + 2] - p10) * i2dr;
-      gr = Px.a * (Pr.a * gr00 + Pr.b * gr01) + Px.b * (Pr.a * gr10 + Pr.b * gr11);
+      const R um = Pr.a * pc[-RL] + Pr.b * pc[1 - RL], u0 = Pr.a * p00 + Pr.b * p01;
+      const R u1 = Pr.a * p10 + Pr.b * p11, u2 = Pr.a * pc[2 * RL] + Pr.b * pc[2 * RL + 1];
+      ph = Px.a * u0 + Px.b * u1;
+      gx = (Px.a * (u1 - um) + Px.b * (u2 - u0)) * i2dx;
+      const R vm = Px.a * pc[-1] + Px.b * pc[RL - 1], v0 = Px.a * p00 + Px.b * p10;
+      const R v1 = Px.a * p01 + Px.b * p11, v2 = Px.a * pc[2] + Px.b * pc[RL + 2];
+      const R d0 = q.R0 + b == 0 ? (R)0 : v1 - vm;
+      gr = (Pr.a * d0 + Pr.b * (v2 - v0)) * i2dr;
+      const Lin<R> Dx = dual_w<R>(a, fx), Dr = dual_w<R>(b, fr);
+      if (M1) {
+        // (the weight products are those of the mode-1 gathers below)
+        ex = interp2w<R, RL>(sm.ex, Dx, Pr);
+        er = interp2w<R, RL>(sm.er, Px, Dr);
+        bt = interp2w<R, RL>(sm.bt, Dx, Dr);
+      } else {
+        ex = interp2<R, RL>(sm.ex, Dx, Pr);
+        er = interp2<R, RL>(sm.er, Px, Dr);
+        bt = interp2<R, RL>(sm.bt, Dx, Dr);
+      }
       if (M1) {
         ex += mode1_at<C, R>(interp2c<C, R, RL>(sm.ex1, Dx, Pr), c, s);
         er += mode1_at<C, R>(interp2c<C, R, RL>(sm.er1, Px, Dr), c, s);
@@ -806,10 +826,16 @@ __global__ __launch_bounds__(WG, (mom_waves_per_simd<R, M1, DEFER, SCAT, O>())) 
   {
     // (SCAT_TILE ranks over whole wavefronts: uniform trip count)
     const int trips = SCAT == SCAT_TILE ? (total + 63) & ~63 : total;
+    // the cell word of the next particle is loaded one turn ahead: the rest of
+    // the record follows it at once (the compiler places those loads behind
+    // the test for a removed particle)
+    unsigned cw_next = kDead;
+    if (threadIdx.x < total) cw_next = pld<NT>(elem(src.cell, slot_of(threadIdx.x)));
     for (int k = threadIdx.x; k < trips; k += WG) {
       const bool valid = SCAT != SCAT_TILE || k < total;
       const int p = slot_of(valid ? k : 0);
-      const unsigned cw = pld<NT>(elem(src.cell, p));
+      const unsigned cw = cw_next;
+      if (k + WG < total) cw_next = pld<NT>(elem(src.cell, slot_of(k + WG)));
       const R fx = pld<NT>(elem(src.fx, p)), fr = pld<NT>(elem(src.fr, p)), th = pld<NT>(elem(src.th, p)), w = pld<NT>(elem(src.w, p));
       R pv[3] = {pld<NT>(elem(src.px, p)), pld<NT>(elem(src.py, p)), pld<NT>(elem(src.pz, p))};
       bool live = valid && cw != kDead;
@@ -965,7 +991,7 @@ template <class R> struct Move {
 template <class R>
 __device__ inline void push_position(const Geo& g, unsigned cw, R fx, R fr, R th, R& py, R& pz, R vx, R vy, R vz,
                                      Move<R>& mv) {
-  const R dt = (R)g.dt, dr = (R)g.dr;
+  const R dt = pick<R>(g.dt, g.dt_f), dr = pick<R>(g.dr, g.dr_f);
   mv.ix0 = cell_ix(cw);
   mv.jr0 = cell_jr(cw);
   mv.fx0 = fx;
@@ -975,7 +1001,7 @@ __device__ inline void push_position(const Geo& g, unsigned cw, R fx, R fr, R th
   mv.vy = vy;
   mv.vz = vz;
   // (|v| <= 1, so the floors below are -1, 0 or 1, whatever the state)
-  const R x1 = fma(vx, (R)g.dtdx, fx);
+  const R x1 = fma(vx, pick<R>(g.dtdx, g.dtdx_f), fx);
   mv.dix = floor_int(x1);
   mv.ix1 = mv.ix0 + mv.dix;
   mv.fx1 = fract_r(x1);
@@ -990,7 +1016,7 @@ __device__ inline void push_position(const Geo& g, unsigned cw, R fx, R fr, R th
   R drad, dth;
   mv.small = radial_step(r, mv.a, mv.b, drad, dth);
   // (the radius stays >= 0 whatever the rounding)
-  const R r1 = clamp_r(fma(drad, (R)g.rdr, fr), max((R)-1, -(R)mv.jr0), (R)1.875);
+  const R r1 = clamp_r(fma(drad, pick<R>(g.rdr, g.rdr_f), fr), max((R)-1, -(R)mv.jr0), (R)1.875);
   mv.djr = floor_int(r1);
   mv.jr1 = mv.jr0 + mv.djr;
   mv.fr1 = fract_r(r1);
@@ -1020,7 +1046,7 @@ __device__ inline void push_position(const Geo& g, unsigned cw, R fx, R fr, R th
 // of its azimuth.
 template <class R>
 __device__ inline void mid_point(const Geo& g, const Move<R>& mv, int& djm, R& frm, R& c, R& s) {
-  const R dr = (R)g.dr, rdr = (R)g.rdr;
+  const R dr = pick<R>(g.dr, g.dr_f), rdr = pick<R>(g.rdr, g.rdr_f);
   const R r0 = ((R)mv.jr0 + mv.fr0) * dr;
   const R u = r0 + (R)0.5 * mv.a, v = (R)0.5 * mv.b;
   R f;
@@ -1109,7 +1135,7 @@ __device__ inline void deposit_current(SmemPos<R, M1>& sm, const Region& q, cons
     R frm, c, s;
     mid_point<R>(g, mv, djm, frm, c, s);
     // the old cell's indices plus a step of at most one: inside the region
-    const R um = fma((R)0.5 * (R)g.dtdx, mv.vx, mv.fx0);
+    const R um = fma(pick<R>(0.5 * g.dtdx, g.hdtdx_f), mv.vx, mv.fx0);
     const int am = a0 + floor_int(um), bm = b0 + djm;
     const R fm = fract_r(um);
     const Lin<R> Px = primal_w<R>(am, fm), Dx = dual_w<R>(am, fm);
@@ -1196,7 +1222,7 @@ __device__ inline void deposit_current2(SmemPos<R, M1>& sm, const Region& q, con
     int djm;
     R frm, c, s;
     mid_point<R>(g, mv, djm, frm, c, s);
-    const R um = fma((R)0.5 * (R)g.dtdx, mv.vx, mv.fx0);
+    const R um = fma(pick<R>(0.5 * g.dtdx, g.hdtdx_f), mv.vx, mv.fx0);
     const int am = a0 + floor_int(um), bm = b0 + djm;
     const R fm = fract_r(um);
     const Quad<R> Qx = quad_primal<R>(am, fm), Ux = quad_dual<R>(am, fm);
