@@ -159,7 +159,7 @@ template <class R> struct State {
   DepositBufs<R> jf;  // filtered currents (chi unused) when the binomial filter is on
   Layout lay[2];
   int* hist;    // particles per tile at the next sort
-  int* arr;     // particles arriving from other tiles at the next (tile) sort
+  int* arr[2];  // particles arriving from other tiles at the next (tile) sort, and at the one after it
   int* sort_stats;  // [incremental, rebuilt] layouts of the tile sorts, gathered cell sorts
   int* ccount;  // particles per cell at the next sort ([phys col][row], as the grids)
   int* ccur;    // per-cell scatter cursors of the next sort
@@ -259,7 +259,7 @@ template <class R> size_t plan(const envpic_params& p, const Sizes& s, bool fp64
     L.mode = cv.take<int>(1);
   }
   S.hist = cv.take<int>((size_t)s.ntiles);
-  S.arr = cv.take<int>((size_t)s.ntiles);
+  for (int b = 0; b < 2; ++b) S.arr[b] = cv.take<int>((size_t)s.ntiles);
   S.sort_stats = cv.take<int>(3);
   S.ccount = cv.take<int>(ng);
   S.ccur = cv.take<int>(ng);
@@ -463,12 +463,11 @@ struct envpic_sim {
     return p.sort_every > 0 && p.sort_every < most ? p.sort_every : most;
   }
   bool presort() const { return n + 1 - sorted_at >= sort_every(); }
-  // the kind of sort at the momentum stage of the next step (0: none);
-  // every CELL_SORT_EVERY-th sort orders the tiles by cell again
-  int next_sort() const {
-    if (!presort()) return 0;
-    return n_sorts % CELL_SORT_EVERY == 0 ? SCAT_CELL : SCAT_TILE;
-  }
+  // the kind of the next sort: every CELL_SORT_EVERY-th orders the tiles by
+  // cell again
+  int sort_kind() const { return n_sorts % CELL_SORT_EVERY == 0 ? SCAT_CELL : SCAT_TILE; }
+  // the kind of sort at the momentum stage of the next step (0: none)
+  int next_sort() const { return presort() ? sort_kind() : SCAT_NONE; }
   bool shift_due() const {
     return p.moving_window && (double)(n + 1) * p.dt >= (double)(shift + 1) * p.dx;
   }
@@ -524,6 +523,7 @@ template <class R> struct SimT : envpic_sim {
     g.base = (int)(sh % sz.nxa);
     const long long c = sh - 2;
     g.t_lo = (int)(c >= 0 ? c / TX : -((-c + TX - 1) / TX));
+    g.t_lo_ring = (g.t_lo % sz.ntxa + sz.ntxa) % sz.ntxa;
     g.dx = p.dx;
     g.dr = p.dr;
     g.dt = p.dt;
@@ -685,9 +685,9 @@ template <class R> struct SimT : envpic_sim {
     // re-sort when the particles have had sort_every() steps to drift from
     // their tiles; in between, p is updated in place
     const bool scatter = n - sorted_at >= sort_every();
-    // every CELL_SORT_EVERY-th sort orders the tiles by cell again (into the
-    // other buffer); the others move only the particles that changed tile
-    const int mode = !scatter ? SCAT_NONE : (n_sorts % CELL_SORT_EVERY == 0 ? SCAT_CELL : SCAT_TILE);
+    // a cell sort writes into the other buffer; a tile sort moves only the
+    // particles that changed tile
+    const int mode = scatter ? sort_kind() : SCAT_NONE;
     const KEvents ev = tick_events();
     // (the position scratch's cell words are free until the position stage)
     launch_momentum<R>(g, S.grids, S.dep[d].chi, S.parts[cur], S.parts[1 - cur], S.lay[lay], S.lay[1 - lay], S.ccur,
@@ -760,7 +760,7 @@ template <class R> struct SimT : envpic_sim {
     inj.pending = S.pending;
     inj.blocks = (shifting && p.profile != ENVPIC_PROFILE_NONE) ? inject_blocks<R>(inj.gn) : 0;
     const KEvents ev = tick_events();
-    const SortCounts sc{next_sort(), S.ccount, S.hist, S.arr};
+    const SortCounts sc{next_sort(), S.ccount, S.hist, S.arr[0]};
     launch_position<R>(g, S.grids, S.dep[n & 1], S.parts[cur], S.lay[lay], sc, shifting ? 1 : 0, S.scr, S.err,
                        sz.max_items, defer, inj, stream, ev);
     tick_end(2, ev);
@@ -786,12 +786,13 @@ template <class R> struct SimT : envpic_sim {
     fa.ccount = S.ccount;
     fa.ccur = S.ccur;
     fa.hist = S.hist;
-    fa.arr = S.arr;
+    fa.arr = S.arr[0];
+    fa.arr_next = S.arr[1];
     fa.in = S.lay[lay];
     fa.out = S.lay[1 - lay];
-    fa.capacity = sz.capacity;
+    fa.capacity = (int)sz.capacity;
     fa.inj_max = p.nr * sz.ppc;
-    fa.reserve = slot_reserve(p, sz);
+    fa.reserve = (int)std::min<long long>(slot_reserve(p, sz), sz.capacity);
     fa.entering = (p.moving_window && p.profile != ENVPIC_PROFILE_NONE) ? ENTERING_TILES : 0;
     fa.max_items = sz.max_items;
     fa.pending = S.pending;
@@ -822,6 +823,7 @@ template <class R> struct SimT : envpic_sim {
       std::swap(G.br1, G.br1_n);
       std::swap(G.bt1, G.bt1_n);
     }
+    if (pre == SCAT_TILE) std::swap(S.arr[0], S.arr[1]);
     tick_end(3, ev);
     n += 1;
     stage = 0;

@@ -117,6 +117,7 @@ struct Geo {
   int ppc_x, ppc_r, ppc_t;
   int base;          // shift mod nxa (physical column of the window's left edge)
   int t_lo;          // lab tile index of column shift - 2
+  int t_lo_ring;     // its ring tile column, t_lo mod ntxa
   long long shift;   // lab column of the window's left edge
   long long cap;     // particle slots per buffer
   double dx, dr, dt;
@@ -207,7 +208,7 @@ __host__ __device__ inline int phys_col(const Geo& g, int rel) { return wrap_col
 
 // lab tile index of ring tile column tcx
 __device__ inline int lab_tile(const Geo& g, int tcx) {
-  int d = tcx - (int)(((long long)g.t_lo % g.ntxa + g.ntxa) % g.ntxa);
+  int d = tcx - g.t_lo_ring;
   if (d < 0) d += g.ntxa;
   return g.t_lo + d;
 }

@@ -163,7 +163,10 @@ __device__ inline ENew<R, M1> ampere(const Geo& g, const Grids<R>& f, const Depo
       const C curl = csub(cscale(cmuli(f.bx1[o]), -irh), cscale(csub(f.bt1[o], f.bt1[om]), idx_));
       e.er1 = cadd(f.er1[o], cscale(csub(curl, din.jr1[o]), dt));
       const C dbr = cscale(csub(f.br1[o], f.br1[om]), idx_);
-      const C dbx = j == 0 ? cscale(f.bx1[o], (R)2 * idr) : cscale(csub(f.bx1[o], f.bx1[o - 1]), idr);
+      // (on the axis bx1[-1] = -bx1[0])
+      const C bx = f.bx1[o], bxm = f.bx1[j == 0 ? o : o - 1];
+      const R sg = j == 0 ? (R)-1 : (R)1;
+      const C dbx = mk<C>((bx.x - sg * bxm.x) * idr, (bx.y - sg * bxm.y) * idr);
       e.et1 = cadd(f.et1[o], cscale(csub(csub(dbr, dbx), din.jt1[o]), dt));
     }
   }
@@ -202,10 +205,11 @@ __device__ inline void tile_node(const Geo& g, const Grids<R>& f, const DepositB
   if (j <= g.nr - 1) f.er_n[o] = ez ? (R)0 : sm.er[k];
   if (i <= g.nx - 1) f.ex_n[o] = sm.ex[k];
   if (M1) {
-    const C z = mk<C>((R)0, (R)0);
+    // (selected by component: a select of pairs goes through scratch memory)
+    const C r1 = sm.er1[k], t1 = sm.et1[k];
     if (i <= g.nx - 1) f.ex1_n[o] = sm.ex1[k];
-    if (j <= g.nr - 1) f.er1_n[o] = ez ? z : sm.er1[k];
-    f.et1_n[o] = ez ? z : sm.et1[k];
+    if (j <= g.nr - 1) f.er1_n[o] = mk<C>(ez ? (R)0 : r1.x, ez ? (R)0 : r1.y);
+    f.et1_n[o] = mk<C>(ez ? (R)0 : t1.x, ez ? (R)0 : t1.y);
   }
   // ---- B^{n+3/2} and Bbar^{n+1}
   if (i <= g.nx - 1 && j <= g.nr - 1) {
@@ -225,7 +229,7 @@ __device__ inline void tile_node(const Geo& g, const Grids<R>& f, const DepositB
       f.bxb1[o] = cscale(cadd(b0, b1), (R)0.5);
     }
     if (i <= g.nx - 1) {
-      const C exr = j == 0 ? cscale(sm.ex1[k + 1], idr) : cscale(sm.ex1[k], recip_r((R)j) * idr);
+      const C exr = cscale(sm.ex1[j == 0 ? k + 1 : k], j == 0 ? idr : recip_r((R)j) * idr);
       const C b0 = bo.br1;
       const C b1 = cadd(b0, cscale(cadd(cmuli(exr), cscale(csub(sm.et1[kp], sm.et1[k]), idx_)), dt));
       f.br1_n[o] = b1;
@@ -352,18 +356,19 @@ __device__ inline void window_row(const Geo& g, const Grids<R>& f, const Deposit
 // --------------------------------------------------------- field stage --
 // One kernel for the field stage, its work groups in three roles: Maxwell
 // tiles (geometry before the shift); if the window moves, the rows of its
-// column resets (geometry after it); before a sort, the per-tile cell scans
-// (two tiles per group).  No role reads another's output.  On a step
-// without a sort, one thread also adds the items and slots of a column
-// injected by the position pass to the layout in use.
+// column resets (geometry after it); before a cell sort, the per-tile cell
+// scans (two tiles per group).  No role reads another's output.  The first
+// group also adds the items and slots of a column injected by the position
+// pass to the layout in use.  (The layout scan stays a launch of its own: as
+// a role of this kernel it took its registers from 43 to 112, held to 64 it
+// spilled, and the stage became 20 to 35 % slower.)
 template <class R, bool M1>
 __global__ __launch_bounds__(MW_T) void k_field(Geo g, Grids<R> f, DepositBufs<R> din, DepositBufs<R> dnext,
                                                DepositBufs<R> d0, DepositBufs<R> d1, FieldArgs fa) {
   __shared__ MwShared<R, M1> sm;
   __shared__ int s_a[MW_T];
   const int blk = blockIdx.x;
-  // an injected column's items and slots join the layout in use
-  if (!fa.presort && blk == 0) bump_pending(fa.gn, fa.in, fa.pending);
+  if (blk == 0) bump_pending(fa.gn, fa.in, fa.pending);
   if (blk < fa.nb_mw) {
     maxwell_tile<R, M1>(g, f, din, dnext, (blk / fa.nbx_mw) * MW_TI, (blk % fa.nbx_mw) * MW_TJ, fa.shifting != 0, sm);
   } else if (blk < fa.nb_mw + fa.nb_win) {
@@ -375,33 +380,29 @@ __global__ __launch_bounds__(MW_T) void k_field(Geo g, Grids<R> f, DepositBufs<R
   }
 }
 
-// before a sort: the injected column's items and slots added to the layout
-// in use, then the next layout (one group): rebuilt from the tile totals
-// before a cell sort, from the arrivals before a tile sort
+// Before a sort: the next layout, rebuilt from the tile totals before a cell
+// sort, from the arrivals before a tile sort.  One group per SCAN_T tiles;
+// each sums all tiles itself (three words a tile, from the L2) instead of
+// waiting for the groups before it.  One group for all tiles, a stretch of
+// them per thread, took 170 us on the 8192 x 768 workload, 33 us on the
+// 4096 x 512 one and 10.5 us on the 2048 x 256 one.
 constexpr int SCAN_T = 1024;
 __global__ __launch_bounds__(SCAN_T) void k_layout_scan(FieldArgs fa) {
-  __shared__ int s_w[SCAN_T / 64];
-  bump_pending(fa.gn, fa.in, fa.pending);
-  __syncthreads();
+  __shared__ long long s_w[SCAN_T / 64];
   if (fa.presort == SCAT_CELL) {
-    full_layout<SCAN_T>(fa.gn, fa.hist, fa.out, fa.capacity, fa.inj_max, fa.reserve, fa.entering, fa.max_items,
-                        fa.err, s_w);
     // The cell order is gathered once the overflow ranges used since the last
     // rebuild exceed 1/32 of the segments: the particles have moved, and a
     // direct scatter of whole records from the momentum pass would write
     // partial cache lines of every record array.  While the particles are
     // still close to cell order the pass scatters them directly (cheaper).
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      const long long seg = fa.in.offsets[fa.gn.ntiles], over = (long long)*fa.in.fill - seg;
-      if (over * 32 > seg) {
-        *fa.out.mode = LAYOUT_FULL | LAYOUT_GATHER;
-        fa.stats[2] += 1;
-      }
-    }
+    const long long seg = fa.in.offsets[fa.gn.ntiles], over = (long long)*fa.in.fill - seg;
+    const bool gather = over * 32 > seg;
+    full_layout<SCAN_T>(fa.gn, fa.hist, fa.out, fa.capacity, fa.inj_max, fa.reserve, fa.entering, fa.max_items,
+                        fa.err, gather ? LAYOUT_FULL | LAYOUT_GATHER : LAYOUT_FULL, s_w);
+    if (gather && blockIdx.x == 0 && threadIdx.x == 0) fa.stats[2] += 1;
   } else {
-    move_layout<SCAN_T>(fa.gn, fa.hist, fa.arr, fa.in, fa.out, fa.capacity, fa.inj_max, fa.reserve, fa.entering,
-                        fa.max_items, fa.err, fa.stats, s_w);
+    move_layout<SCAN_T>(fa.gn, fa.hist, fa.arr, fa.arr_next, fa.in, fa.out, fa.capacity, fa.inj_max, fa.reserve,
+                        fa.entering, fa.max_items, fa.err, fa.stats, s_w);
   }
 }
 
@@ -473,7 +474,7 @@ void launch_field(const Geo& g, const Grids<R>& f, const DepositBufs<R>& din, co
     launch_k(k_field<R, true>, dim3(grid), dim3(MW_T), st, ev_field, g, f, din, dnext, d0, d1, fa);
   else
     launch_k(k_field<R, false>, dim3(grid), dim3(MW_T), st, ev_field, g, f, din, dnext, d0, d1, fa);
-  if (fa.presort) launch_k(k_layout_scan, dim3(1), dim3(SCAN_T), st, KEvents{nullptr, ev.stop}, fa);
+  if (fa.presort) launch_k(k_layout_scan, dim3((g.ntiles + SCAN_T - 1) / SCAN_T), dim3(SCAN_T), st, KEvents{nullptr, ev.stop}, fa);
 }
 
 // ------------------------------------------------- binomial J filter --

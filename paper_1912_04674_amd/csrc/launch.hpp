@@ -91,10 +91,11 @@ struct FieldArgs {
   int* ccur;
   int* hist;                   // particles per tile after the sort
   int* arr;                    // arrivals per tile (tile sorts)
+  int* arr_next;               // those of the next tile sort, cleared
   Layout in;                   // the layout in use
   Layout out;                  // the next layout
-  long long capacity;
-  long long reserve;           // slots kept free past the segments when a layout is rebuilt
+  int capacity;                // (slots < 2^30)
+  int reserve;                 // slots kept free past the segments when a layout is rebuilt
   int entering;                // tile columns ahead of the window given a full tile of slots when it is rebuilt
   int inj_max, max_items;
   int* pending;

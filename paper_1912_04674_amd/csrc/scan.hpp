@@ -2,8 +2,7 @@
 // of its cells' counts into the per-cell cursors (work groups of the
 // field-stage kernel); over all tiles, the scans of the tile totals into the
 // next layout's segments and work items, or of the arrivals into the free
-// slots and overflow ranges of an incremental sort (one work group,
-// launched after it).
+// slots and overflow ranges of an incremental sort (launched after it).
 #pragma once
 #include "common.hpp"
 
@@ -43,31 +42,42 @@ __device__ inline void cell_scan_tile(const Geo& g, int t, int lt, int* ccount, 
   if (active && lt == TX * TR - 1) hist[t] = s[lt];
 }
 
-// Exclusive scan of one int per thread over the NT threads of a block
-// (NT a multiple of 64, at most 64 wavefronts): shuffles inside each
-// wavefront, then the wavefront totals through s_w (NT / 64 ints).  Returns
-// the sum of the lower threads' values; *total gets the block's sum.  Every
-// thread calls it.
-template <int NT> __device__ inline int block_scan(int v, int* s_w, int* total) {
+// Exclusive scan of two non-negative sums per thread (in the halves of one
+// word) over the NT threads of a block (NT a multiple of 64, at most 64
+// wavefronts): shuffles inside each wavefront, then the wavefront totals
+// through s_w (NT / 64 words).  Returns the sums of the lower threads' values;
+// *total gets the block's.  Every thread calls it.
+struct Pair {
+  int a, b;
+};
+__device__ inline long long pack_pair(int a, int b) { return ((long long)a << 32) | (unsigned)b; }
+template <int NT> __device__ inline Pair block_scan(int a, int b, long long* s_w, Pair* total) {
   const int lane = (int)(threadIdx.x & 63), w = (int)(threadIdx.x >> 6);
-  int x = v;
+  const long long v = pack_pair(a, b);
+  long long x = v;
   for (int o = 1; o < 64; o <<= 1) {
-    const int y = __shfl_up(x, o, 64);
+    const long long y = __shfl_up(x, o, 64);
     if (lane >= o) x += y;
   }
   if (lane == 63) s_w[w] = x;
   __syncthreads();
-  int pre = 0, tot = 0;
+  long long pre = 0, tot = 0;
   for (int k = 0; k < NT / 64; ++k) {
-    const int t = s_w[k];
+    const long long t = s_w[k];
     pre += k < w ? t : 0;
     tot += t;
   }
   __syncthreads();  // s_w is free again
-  *total = tot;
-  return pre + x - v;
+  *total = Pair{(int)(tot >> 32), (int)tot};
+  const long long e = pre + x - v;
+  return Pair{(int)(e >> 32), (int)e};
 }
-
+// the block's sum of two values per thread, in every thread
+template <int NT> __device__ inline Pair block_sum(int a, int b, long long* s_w) {
+  Pair t;
+  block_scan<NT>(a, b, s_w, &t);
+  return t;
+}
 // The items (pending[0]) and slots past the used ones (pending[1]) of a
 // column injected since the last scan join layout L, the layout in use: an
 // item placed at the end of its tile's segment extends the segment's used
@@ -94,13 +104,13 @@ __device__ inline void bump_pending(const Geo& g, Layout L, int* pending) {
 // item_share particles (the last holds the rest), written from items[em] on
 // (none past max_em); returns their number.
 __device__ inline int emit_items(const Geo& g, int4* items, int em, int max_em, int key, int st, int v,
-                                 long long capacity) {
+                                 int capacity) {
   const int nm = (v + g.chunk - 1) / g.chunk, sh = item_share(v, g.chunk);
   for (int k = 0; k < nm; ++k) {
     const int lo = k * sh, hi = min(lo + sh, v);
     // items never reach past the buffer (an overflow is flagged by the caller)
     if (em + k < max_em)
-      items[em + k] = ((long long)st + hi <= capacity) ? make_int4(key, st + lo, hi - lo, 0) : make_int4(key, 0, 0, 0);
+      items[em + k] = (st + hi <= capacity) ? make_int4(key, st + lo, hi - lo, 0) : make_int4(key, 0, 0, 0);
   }
   return nm;
 }
@@ -120,138 +130,147 @@ __device__ inline int seg_room(const Geo& g, int t, int v, int entering, int ali
   int room = v;
   if (entering > 0) {
     const int tcx = t / g.ntr, tr = t - (t / g.ntr) * g.ntr;
-    const long long T = lab_tile(g, tcx), front = (g.shift + g.nx - 1) / TX;
+    const int T = lab_tile(g, tcx), front = (int)(g.shift + g.nx - 1) / TX;  // (lab columns fit 20 bits)
     if (T >= front && T <= front + entering)
       room = max(v, TX * min(TR, g.nr - tr * TR) * g.ppc_x * g.ppc_r * g.ppc_t);
   }
   return round_slots(room, align);
 }
 
-// One block of NT threads: the tile totals in hist become layout `out` of
-// the other buffer, the whole layout rebuilt: the segment of a tile of v
-// particles holds seg_room slots (the room for entering tiles, and the
-// alignment of the segments, only when `reserve` slots past the segments
-// stay free), and its particles form ceil(v / chunk) items.  hist stays (the kernels keep it
-// current).  Flags when the particles plus the columns injected before the
-// next sort would not fit.
+// The tile totals in hist become layout `out` of the other buffer, the whole
+// layout rebuilt, by one block of NT threads per NT tiles: the segment of a
+// tile of v particles holds seg_room slots (the room for entering tiles, and
+// the alignment of the segments, only when `reserve` slots past the segments
+// stay free), and its particles form ceil(v / chunk) items.  hist stays (the
+// kernels keep it current).  Flags when the particles plus the columns
+// injected before the next sort would not fit.
 template <int NT>
-__device__ inline void full_layout(const Geo& g, int* hist, Layout out, long long capacity, int inj_max,
-                                   long long reserve, int entering, int max_items, int* err, int* s_w) {
-  const int nt = g.ntiles;
-  const int tid = threadIdx.x;
-  const int per = (nt + NT - 1) / NT;
-  const int t0 = min(nt, tid * per), t1 = min(nt, t0 + per);
-  int c = 0, m = 0, rs = 0;
-  for (int t = t0; t < t1; ++t) {
-    const int v = hist[t];
-    c += v;
-    rs += seg_room(g, t, v, entering, 1);
-    m += (v + g.chunk - 1) / g.chunk;
+__device__ inline void full_layout(const Geo& g, const int* hist, Layout out, int capacity, int inj_max, int reserve,
+                                   int entering, int max_items, int* err, int mode, long long* s_w) {
+  const int nt = g.ntiles, first = blockIdx.x * NT, t = first + threadIdx.x;
+  // over all tiles and over those before this block's: the segments' size
+  // with and without the room for entering tiles, packed and aligned, and
+  // the items
+  int r[5] = {0, 0, 0, 0, 0}, q[5] = {0, 0, 0, 0, 0};
+  for (int k = threadIdx.x; k < nt; k += NT) {
+    const int v = hist[k];
+    const int x[5] = {v, round_slots(v, SLOT_ALIGN), seg_room(g, k, v, entering, 1),
+                      seg_room(g, k, v, entering, SLOT_ALIGN), (v + g.chunk - 1) / g.chunk};
+    for (int e = 0; e < 5; ++e) {
+      r[e] += x[e];
+      q[e] += k < first ? x[e] : 0;
+    }
   }
-  int total_c = 0, n_items = 0, total_rs = 0, seg_end = 0;
-  block_scan<NT>(c, s_w, &total_c);
-  int em = block_scan<NT>(m, s_w, &n_items);
-  block_scan<NT>(rs, s_w, &total_rs);
-  const int ent = (long long)total_rs + reserve <= capacity ? entering : 0;
-  int cs = 0, ca = 0, aligned_end = 0;
-  for (int t = t0; t < t1; ++t) {
-    cs += seg_room(g, t, hist[t], ent, 1);
-    ca += seg_room(g, t, hist[t], ent, SLOT_ALIGN);
-  }
-  int ec = block_scan<NT>(cs, s_w, &seg_end);
-  const int eca = block_scan<NT>(ca, s_w, &aligned_end);
-  int align = 1;
-  if ((long long)aligned_end + reserve <= capacity) {
-    align = SLOT_ALIGN;
-    ec = eca;
-    seg_end = aligned_end;
-  }
+  const Pair none = block_sum<NT>(r[0], r[1], s_w), with = block_sum<NT>(r[2], r[3], s_w);
+  const int ent = with.a <= capacity - reserve ? entering : 0;
+  const Pair room = ent > 0 ? with : none;
+  const int align = room.b <= capacity - reserve ? SLOT_ALIGN : 1;
+  const int seg_end = align > 1 ? room.b : room.a;
+  const int items = block_sum<NT>(r[4], 0, s_w).a;
+  const int before = align > 1 ? (ent > 0 ? q[3] : q[1]) : (ent > 0 ? q[2] : q[0]);
+  const Pair base = block_sum<NT>(before, q[4], s_w);
   // room kept for the columns injected before the next sort (one per step)
   const int item_cap = max_items - SORT_EVERY * g.ntr;
-  for (int t = t0; t < t1; ++t) {
-    const int v = hist[t];
-    out.offsets[t] = ec;
+  const int v = t < nt ? hist[t] : 0;
+  Pair tot;
+  const Pair pre =
+      block_scan<NT>(t < nt ? seg_room(g, t, v, ent, align) : 0, (v + g.chunk - 1) / g.chunk, s_w, &tot);
+  if (t < nt) {
+    const int st = base.a + pre.a;
+    out.offsets[t] = st;
     out.ext[t] = v;
-    out.cursor[t] = ec;
+    out.cursor[t] = st;
     out.ovb[t] = 0;
     out.ovn[t] = 0;
-    em += emit_items(g, out.items, em, item_cap, t, ec, v, capacity);
-    ec += seg_room(g, t, v, ent, align);
+    emit_items(g, out.items, base.b + pre.b, item_cap, t, st, v, capacity);
   }
-  if (tid == NT - 1) {
+  if (t == 0) {
     out.offsets[nt] = seg_end;
     *out.fill = seg_end;
-    *out.n_items = min(n_items, item_cap);
-    *out.mode = LAYOUT_FULL;
-    if (n_items > item_cap) atomicOr(err, ERR_ITEMS);
-    if ((long long)seg_end + (long long)SORT_EVERY * inj_max > capacity) atomicOr(err, ERR_CAPACITY);
+    *out.n_items = min(items, item_cap);
+    *out.mode = mode;
+    if (items > item_cap) atomicOr(err, ERR_ITEMS);
+    if (seg_end > capacity - SORT_EVERY * inj_max) atomicOr(err, ERR_CAPACITY);
   }
 }
 
-// One block of NT threads, before a tile sort: layout `out` of the same
-// buffer as `in`, where only the particles that change tile move.  arr[t]
-// holds the arrivals of tile t (particles of other tiles' items whose cell
-// is now in t, and every particle of t's items past the segments: injected
-// columns, earlier overflows), hist[t] its particles after the sort.  The
-// arrivals fill the free slots at the end of t's segment, then a range of
+// Before a tile sort, by one block of NT threads per NT tiles: layout `out`
+// of the same buffer as `in`, where only the particles that change tile move.
+// arr[t] holds the arrivals of tile t (particles of other tiles' items whose
+// cell is now in t, and every particle of t's items past the segments:
+// injected columns, earlier overflows), hist[t] its particles after the sort.
+// The arrivals fill the free slots at the end of t's segment, then a range of
 // their own past the used slots (from ovb[t], ovn[t] of them).  When the
 // overflow or the items would not fit, the layout is rebuilt as by
 // full_layout instead (mode LAYOUT_FULL: the sort then scatters every
-// particle).  arr is cleared; stats[0] counts the incremental layouts,
-// stats[1] the rebuilt ones.
+// particle).  arr_next, the arrivals of the next tile sort, is cleared (arr
+// itself is still read by other blocks); stats[0] counts the incremental
+// layouts, stats[1] the rebuilt ones.
 template <int NT>
-__device__ inline void move_layout(const Geo& g, int* hist, int* arr, Layout in, Layout out, long long capacity,
-                                   int inj_max, long long reserve, int entering, int max_items, int* err, int* stats,
-                                   int* s_w) {
-  const int nt = g.ntiles;
-  const int tid = threadIdx.x;
-  const int per = (nt + NT - 1) / NT;
-  const int t0 = min(nt, tid * per), t1 = min(nt, t0 + per);
+__device__ inline void move_layout(const Geo& g, const int* hist, const int* arr, int* arr_next, Layout in, Layout out,
+                                   int capacity, int inj_max, int reserve, int entering, int max_items, int* err,
+                                   int* stats, long long* s_w) {
+  const int nt = g.ntiles, first = blockIdx.x * NT, t = first + threadIdx.x;
   const int seg_end = in.offsets[nt];
   const int fill0 = *in.fill;
-  int ov = 0, m = 0;
-  for (int t = t0; t < t1; ++t) {
-    const int a = arr[t], e = in.ext[t], cap = in.offsets[t + 1] - in.offsets[t];
-    const int tail = min(a, cap - e);
-    ov += a - tail;
-    m += (e + tail + g.chunk - 1) / g.chunk;
-    if (!overflow_rides(g, e + tail, a - tail)) m += (a - tail + g.chunk - 1) / g.chunk;
+  // arrivals of tile k: `tail` into its segment's free slots (e in use),
+  // `ov` past the segments; `items` of both
+  struct Plan {
+    int e, tail, ov, items;
+  };
+  auto plan = [&](int k) {
+    Plan p;
+    const int a = arr[k];
+    p.e = in.ext[k];
+    p.tail = min(a, in.offsets[k + 1] - in.offsets[k] - p.e);
+    p.ov = a - p.tail;
+    p.items = (p.e + p.tail + g.chunk - 1) / g.chunk;
+    if (!overflow_rides(g, p.e + p.tail, p.ov)) p.items += (p.ov + g.chunk - 1) / g.chunk;
+    return p;
+  };
+  if (t < nt) arr_next[t] = 0;
+  const Plan p = t < nt ? plan(t) : Plan{0, 0, 0, 0};
+  Pair all, base{0, 0};
+  const Pair pre = block_scan<NT>(p.ov, p.items, s_w, &all);
+  if (nt > NT) {
+    // all tiles, and those before this block's
+    int ov = 0, m = 0, ov_before = 0, m_before = 0;
+    for (int k = threadIdx.x; k < nt; k += NT) {
+      const Plan x = plan(k);
+      ov += x.ov;
+      m += x.items;
+      ov_before += k < first ? x.ov : 0;
+      m_before += k < first ? x.items : 0;
+    }
+    all = block_sum<NT>(ov, m, s_w);
+    base = block_sum<NT>(ov_before, m_before, s_w);
   }
-  int total_ov = 0, n_items = 0;
-  const int ov_pre = block_scan<NT>(ov, s_w, &total_ov);
-  int em = block_scan<NT>(m, s_w, &n_items);
-  const long long fill_new = (long long)fill0 + total_ov;
+  const int fill_new = fill0 + all.a;
   const int item_cap = max_items - SORT_EVERY * g.ntr;
-  if (fill_new + (long long)SORT_EVERY * inj_max > capacity || n_items > item_cap) {
-    // every thread takes the same branch
-    __syncthreads();
-    if (tid == 0) stats[1] += 1;
-    for (int t = t0; t < t1; ++t) arr[t] = 0;
-    full_layout<NT>(g, hist, out, capacity, inj_max, reserve, entering, max_items, err, s_w);
+  if (fill_new > capacity - SORT_EVERY * inj_max || all.b > item_cap) {
+    // every thread of every block takes the same branch
+    if (t == 0) stats[1] += 1;
+    full_layout<NT>(g, hist, out, capacity, inj_max, reserve, entering, max_items, err, LAYOUT_FULL, s_w);
     return;
   }
-  int ob = fill0 + ov_pre;
-  for (int t = t0; t < t1; ++t) {
-    const int a = arr[t], e = in.ext[t], base = in.offsets[t], cap = in.offsets[t + 1] - base;
-    const int tail = min(a, cap - e);
-    out.offsets[t] = base;
-    out.ext[t] = e + tail;
+  if (t < nt) {
+    const int ob = fill0 + base.a + pre.a, n = p.e + p.tail, st = in.offsets[t];
+    int em = base.b + pre.b;
+    out.offsets[t] = st;
+    out.ext[t] = n;
     out.cursor[t] = 0;
     out.ovb[t] = ob;
-    out.ovn[t] = a - tail;
-    em += emit_items(g, out.items, em, item_cap, t, base, e + tail, capacity);
-    if (overflow_rides(g, e + tail, a - tail)) {
-      if (em <= item_cap) out.items[em - 1].w = a - tail;
-    } else {
-      em += emit_items(g, out.items, em, item_cap, t, ob, a - tail, capacity);
-    }
-    ob += a - tail;
-    arr[t] = 0;
+    out.ovn[t] = p.ov;
+    em += emit_items(g, out.items, em, item_cap, t, st, n, capacity);
+    if (overflow_rides(g, n, p.ov))
+      out.items[em - 1].w = p.ov;
+    else
+      emit_items(g, out.items, em, item_cap, t, ob, p.ov, capacity);
   }
-  if (tid == NT - 1) {
+  if (t == 0) {
     out.offsets[nt] = seg_end;
-    *out.fill = (int)fill_new;
-    *out.n_items = n_items;
+    *out.fill = fill_new;
+    *out.n_items = all.b;
     *out.mode = LAYOUT_MOVE;
     stats[0] += 1;
   }
