@@ -12,7 +12,7 @@
 //     sort by tile runs every third step (every second with quadratic
 //     shapes); it moves only the particles that changed tile (into free
 //     slots of their new tile's segment, or into an overflow range of that
-//     tile past all segments), and every CELL_SORT_EVERY-th sort rebuilds
+//     tile past all segments), and one in CELL_SORT_EVERY sorts rebuilds
 //     the whole layout, ordered by cell, in the second buffer (the two
 //     buffers ping-pong at those sorts);
 //   * the envelope rows j = 0, 1 additionally in FP64 (FP32 mode).
@@ -42,8 +42,8 @@ constexpr int CRN = CR * CR;
 // how a sort moves the particles: by tile (only the particles that changed
 // tile move; if the layout has no room for them, every particle is
 // scattered into the other buffer and copied back), or by cell with the
-// placement of loading (every CELL_SORT_EVERY-th sort, into the other
-// buffer)
+// placement of loading (one in CELL_SORT_EVERY sorts at the default sort
+// period, into the other buffer)
 constexpr int SCAT_NONE = 0, SCAT_TILE = 1, SCAT_CELL = 2;
 constexpr int CELL_SORT_EVERY = 8;
 // the layout a scan produced for a tile sort: incremental, or every particle
