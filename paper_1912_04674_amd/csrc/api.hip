@@ -280,6 +280,7 @@ template <class R> size_t plan(const envpic_params& p, const Sizes& s, bool fp64
     S.cg.p2 = cv.take<double>(nu);
     S.cg.q = cv.take<double>(nu);
     S.cg.idiag = cv.take<double>((size_t)p.nr);
+    S.cg.sine = cv.take<float>(cg_sine_modes(p.nx, p.nr) ? 2 * (size_t)p.nx : 0);
     S.cg.part = cv.take<double>((size_t)cg_blocks(p.nx, p.nr) * 2);
     S.cg.s = cv.take<double>(CG_NS);
   }

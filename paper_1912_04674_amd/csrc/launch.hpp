@@ -153,14 +153,20 @@ void launch_beam(const Geo& g, const Parts<R>& P, const Layout& L, int max_items
 // gradients on the (nx - 1) x nr interior potential nodes, FP64
 constexpr int CG_CHECK = 25;  // iterations between residual reads
 constexpr int CG_NS = 8;      // device scalars
+// Largest grid whose solve uses the sine modes along x as preconditioner: the
+// sine table (8 bytes per column) and a mode's radial system (24 bytes per
+// row) fit a work group's LDS.
+constexpr int PRE_NX_MAX = 16384, PRE_NJ_MAX = 4096;
 struct CgVecs {
   double *x, *r, *p, *p2, *q;  // [unknowns] each (p, p2: two direction buffers)
   double* idiag;          // [nr] inverse diagonal of each row
+  float* sine;            // [2 nx] sin(pi t / nx) (grids up to PRE_NX_MAX)
   double* part;           // [blocks][2] partial sums
   double* s;              // [CG_NS]
 };
 long long cg_unknowns(int nx, int nr);
 int cg_blocks(int nx, int nr);
+bool cg_sine_modes(int nx, int nr);
 template <class R>
 int bunch_solve(const Geo& g, const Parts<R>& P, const Layout& L, int max_items, const Grids<R>& f,
                 unsigned id_lo, unsigned id_hi, double beta, double tol, int max_iter, const CgVecs& v,
