@@ -9,6 +9,7 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -435,6 +436,8 @@ struct envpic_sim {
     }
     for (hipEvent_t e : ev_pool) (void)hipEventDestroy(e);
   }
+  std::mutex io;  // held by the calls that read state back through shared scratch memory
+
   virtual int init() = 0;
   virtual int momentum(bool defer) = 0;
   virtual int project(int what) = 0;
@@ -443,7 +446,7 @@ struct envpic_sim {
   virtual int field() = 0;
   virtual int get_field(int f, double* out) = 0;
   virtual int set_field(int f, const double* in) = 0;
-  virtual int get_particles(std::vector<double>* cols, std::vector<uint32_t>* ids) = 0;
+  virtual int read_particles(double* const* outs, uint32_t* id, int64_t* count) = 0;
   virtual int set_particles(int64_t n, const double* const* cols, const uint32_t* id) = 0;
   virtual int diagnostics(double* out) = 0;
   virtual int diagnostics_noalloc(double* dev_out) = 0;
@@ -881,43 +884,24 @@ template <class R> struct SimT : envpic_sim {
     return fail(ENVPIC_EINVAL, "unknown field");
   }
 
+  // Packed as FP64 on the device and copied straight to the caller (a copy of
+  // the padded grid converted by one host thread took ten times as long).  The
+  // bunch solve's vectors hold it: 5 (nx-1) nr doubles are never fewer than
+  // 2 (nx+1) (nr+1) on the grids accepted (nx >= 4, nr >= 2), and each use of
+  // them ends before its call returns.
   int get_field(int f, double* out) override {
     FieldRef r;
     int rc = field_ref(f, r);
     if (rc) return rc;
-    const int comp = r.cplx ? 2 : 1;
-    std::vector<R> buf(sz.ngrid * comp);
-    if ((rc = hip_check(hipMemcpyAsync(buf.data(), r.ptr, buf.size() * sizeof(R), hipMemcpyDeviceToHost, stream), "get_field"))) return rc;
-    std::vector<double2> ax;
+    const std::lock_guard<std::mutex> lock(io);
     const bool env = f == ENVPIC_F_ENV || f == ENVPIC_F_ENV_PREV;
-    if (fp64_rows && env) {
-      ax.resize((size_t)sz.nxa * 2);
-      const double2* src = f == ENVPIC_F_ENV ? S.grids.ax : S.grids.axp;
-      if ((rc = hip_check(hipMemcpyAsync(ax.data(), src, ax.size() * sizeof(double2), hipMemcpyDeviceToHost, stream), "get_field rows"))) return rc;
-    }
-    if ((rc = hip_check(hipStreamSynchronize(stream), "get_field sync"))) return rc;
-    const Geo g = geo();
-    const int nr1 = p.nr + 1;
-    for (int i = 0; i <= p.nx; ++i) {
-      const int pc = phys_col(g, i);
-      for (int j = 0; j <= p.nr; ++j) {
-        const bool valid = (!r.dual_x || i <= p.nx - 1) && (!r.dual_r || j <= p.nr - 1);
-        const size_t o = (size_t)pc * sz.pitch + j;
-        const size_t k = (size_t)i * nr1 + j;
-        if (r.cplx) {
-          double re = valid ? (double)buf[2 * o] : 0.0, im = valid ? (double)buf[2 * o + 1] : 0.0;
-          if (fp64_rows && env && j <= 1) {
-            re = ax[pc * 2 + j].x;
-            im = ax[pc * 2 + j].y;
-          }
-          out[2 * k] = re;
-          out[2 * k + 1] = im;
-        } else {
-          out[k] = valid ? (double)buf[o] : 0.0;
-        }
-      }
-    }
-    return ENVPIC_OK;
+    ExportField e{r.ptr, nullptr, r.cplx, r.dual_x, r.dual_r};
+    if (fp64_rows && env) e.rows = f == ENVPIC_F_ENV ? S.grids.ax : S.grids.axp;
+    launch_export_field<R>(geo(), e, S.cg.x, stream);
+    if ((rc = launched("get_field"))) return rc;
+    const size_t nd = (size_t)(p.nx + 1) * (p.nr + 1) * (r.cplx ? 2 : 1);
+    if ((rc = hip_check(hipMemcpyAsync(out, S.cg.x, nd * sizeof(double), hipMemcpyDeviceToHost, stream), "get_field"))) return rc;
+    return hip_check(hipStreamSynchronize(stream), "get_field sync");
   }
 
   int set_field(int f, const double* in) override {
@@ -982,7 +966,36 @@ template <class R> struct SimT : envpic_sim {
     return ENVPIC_OK;
   }
 
-  int get_particles(std::vector<double>* cols, std::vector<uint32_t>* ids) override {
+  // The live particles in ascending id order, to the columns asked for (the
+  // others null).  Between steps the device orders and converts them in the
+  // particle buffer that is not in use (1 M particles and 8 fields of 1024 x 128
+  // cells: 9.6 ms, 65 to 75 with one host thread sorting and converting); the
+  // host does it within a step, where that buffer may hold a sort
+  // still to be copied back, and for ids that occur twice or are too sparse
+  // for their bitmap.
+  int read_particles(double* const* outs, uint32_t* id, int64_t* count) override {
+    const std::lock_guard<std::mutex> lock(io);
+    if (stage == 0 && !settle_due) {
+      const Parts<R>& F = S.parts[1 - cur];
+      char* scratch = reinterpret_cast<char*>(F.cell);
+      const size_t bytes = (size_t)(reinterpret_cast<char*>(F.id + sz.capacity) - scratch);
+      const int rc = export_particles<R>(geo(), S.parts[cur], S.lay[lay], sz.max_items, scratch, bytes, outs, id,
+                                         count, stream);
+      if (rc == 0) return launched("get_particles");
+      if (rc < 0) return fail(ENVPIC_EDEVICE, "get_particles");
+    }
+    std::vector<double> cols[7];
+    std::vector<uint32_t> ids;
+    int rc = sort_particles(cols, &ids);
+    if (rc) return rc;
+    *count = (int64_t)ids.size();
+    for (int c = 0; c < 7; ++c)
+      if (outs[c] && !cols[c].empty()) std::memcpy(outs[c], cols[c].data(), cols[c].size() * sizeof(double));
+    if (id && !ids.empty()) std::memcpy(id, ids.data(), ids.size() * sizeof(uint32_t));
+    return ENVPIC_OK;
+  }
+
+  int sort_particles(std::vector<double>* cols, std::vector<uint32_t>* ids) {
     int used = 0;
     std::vector<char> covered;
     int rc = used_slots(used, covered);
@@ -1350,15 +1363,9 @@ int envpic_state(const envpic_sim* s, int64_t* n, int64_t* shift, int64_t* n_par
 int envpic_get_particles(const envpic_sim* s, double* x, double* y, double* z, double* px, double* py, double* pz,
                          double* w, uint32_t* id) {
   if (!s) return fail(ENVPIC_EINVAL, "NULL sim");
-  std::vector<double> cols[7];
-  std::vector<uint32_t> ids;
-  int rc = const_cast<envpic_sim*>(s)->get_particles(cols, &ids);
-  if (rc) return rc;
   double* outs[7] = {x, y, z, px, py, pz, w};
-  for (int c = 0; c < 7; ++c)
-    if (outs[c] && !cols[c].empty()) std::memcpy(outs[c], cols[c].data(), cols[c].size() * sizeof(double));
-  if (id && !ids.empty()) std::memcpy(id, ids.data(), ids.size() * sizeof(uint32_t));
-  return ENVPIC_OK;
+  int64_t n = 0;
+  return const_cast<envpic_sim*>(s)->read_particles(outs, id, &n);
 }
 
 int envpic_set_particles(envpic_sim* s, int64_t n, const double* x, const double* y, const double* z,
@@ -1455,13 +1462,13 @@ int envpic_save(const envpic_sim* cs, void* blob, size_t* bytes) {
   envpic_sim* s = const_cast<envpic_sim*>(cs);
   if (!s || !bytes) return fail(ENVPIC_EINVAL, "NULL argument");
   if (s->stage != 0) return fail(ENVPIC_EORDER, "save only between steps");
-  std::vector<double> cols[7];
-  std::vector<uint32_t> ids;
-  int rc = s->get_particles(cols, &ids);
+  double* cols[7] = {};
+  int64_t np = 0;
+  int rc = s->read_particles(cols, nullptr, &np);  // (their number)
   if (rc) return rc;
   size_t need = sizeof(BlobHeader);
   for (int k = 0; k < n_ckpt_fields(s->p); ++k) need += field_doubles(s->p, kCkptFields[k]) * sizeof(double);
-  need += ids.size() * (7 * sizeof(double) + sizeof(uint32_t));
+  need += (size_t)np * (7 * sizeof(double) + sizeof(uint32_t));
   if (!blob) {
     *bytes = need;
     return ENVPIC_OK;
@@ -1478,7 +1485,7 @@ int envpic_save(const envpic_sim* cs, void* blob, size_t* bytes) {
   h.nfields = n_ckpt_fields(s->p);
   h.n = s->n;
   h.shift = s->shift;
-  h.nparticles = (int64_t)ids.size();
+  h.nparticles = np;
   h.params = s->p;
   std::memcpy(q, &h, sizeof h);
   q += sizeof h;
@@ -1487,10 +1494,10 @@ int envpic_save(const envpic_sim* cs, void* blob, size_t* bytes) {
     q += field_doubles(s->p, kCkptFields[k]) * sizeof(double);
   }
   for (int c = 0; c < 7; ++c) {
-    if (!ids.empty()) std::memcpy(q, cols[c].data(), ids.size() * sizeof(double));
-    q += ids.size() * sizeof(double);
+    cols[c] = (double*)q;
+    q += (size_t)np * sizeof(double);
   }
-  if (!ids.empty()) std::memcpy(q, ids.data(), ids.size() * sizeof(uint32_t));
+  if ((rc = s->read_particles(cols, (uint32_t*)q, &np))) return rc;
   *bytes = need;
   return ENVPIC_OK;
 }

@@ -172,4 +172,15 @@ int bunch_solve(const Geo& g, const Parts<R>& P, const Layout& L, int max_items,
                 unsigned id_lo, unsigned id_hi, double beta, double tol, int max_iter, const CgVecs& v,
                 hipStream_t st, int* iters, double* resid);
 
+// state read back by the host (export.hip)
+struct ExportField {
+  const void* ptr;      // the grid, real or complex
+  const double2* rows;  // FP64 values of rows j <= 1 (null: those of the grid)
+  bool cplx, dual_x, dual_r;
+};
+template <class R> void launch_export_field(const Geo& g, const ExportField& f, double* out, hipStream_t st);
+template <class R>
+int export_particles(const Geo& g, const Parts<R>& P, const Layout& L, int max_items, char* scratch, size_t bytes,
+                     double* const* outs, uint32_t* ids, int64_t* n, hipStream_t st);
+
 }  // namespace envpic

@@ -252,7 +252,7 @@ class Sim:
         buf = np.zeros(shape[0] * shape[1] * (2 if cplx else 1))
         _check(lib().envpic_get_field(self._h, FIELDS[name], _dptr(buf)))
         if cplx:
-            return (buf[0::2] + 1j * buf[1::2]).reshape(shape)
+            return buf.view(np.complex128).reshape(shape)
         return buf.reshape(shape)
 
     def set_field(self, name, arr):
