@@ -267,12 +267,15 @@ template <class R> size_t plan(const envpic_params& p, const Sizes& s, bool fp64
   S.err = cv.take<int>(1);
   S.pending = cv.take<int>(2);
   S.diag_scratch = cv.take<double>((size_t)diag_scratch_doubles());
-  S.diag_out = cv.take<double>(ENVPIC_NDIAG);
+  S.diag_out = cv.take<double>(ENVPIC_NDIAG + 1);  // the sums, then the error word
   S.beam.hist = cv.take<unsigned long long>(BEAM_MAX_BINS);
-  S.beam.hist_f = cv.take<double>(BEAM_MAX_BINS);
   S.beam.part = cv.take<double>((size_t)s.max_items * BEAM_PARTS);
   S.beam.st = cv.take<double>(BEAM_STATE);
-  S.beam.out = cv.take<double>(ENVPIC_NBEAM);
+  // (a work item and its riders, or a row tile of an injected column)
+  S.beam.item_words = (std::max(s.chunk + std::min(MAX_RIDERS, s.chunk / 2), TR * s.ppc) + 63) / 64;
+  S.beam.bits = cv.take<unsigned long long>((size_t)s.max_items * S.beam.item_words);
+  S.beam.out = cv.take<double>(ENVPIC_NBEAM + 1 + BEAM_MAX_BINS);
+  S.beam.hist_f = S.beam.out + ENVPIC_NBEAM + 1;
   {
     const size_t nu = (size_t)cg_unknowns(p.nx, p.nr);
     S.cg.x = cv.take<double>(nu);
@@ -686,6 +689,9 @@ template <class R> struct SimT : envpic_sim {
     int rc = hip_check(hipMemcpyAsync(&e, S.err, sizeof(int), hipMemcpyDeviceToHost, stream), "read error word");
     if (rc) return rc;
     if ((rc = hip_check(hipStreamSynchronize(stream), "sync"))) return rc;
+    return err_code(e);
+  }
+  int err_code(int e) {
     if (e & ERR_CAPACITY) return fail(ENVPIC_ENOMEM, "particle capacity exceeded");
     if (e & ERR_ITEMS) return fail(ENVPIC_ENOMEM, "work-item list overflow");
     if (e & ERR_LAYOUT) return fail(ENVPIC_EDEVICE, "a sort met more particles changing tile than its scan counted");
@@ -1100,12 +1106,14 @@ template <class R> struct SimT : envpic_sim {
   int diagnostics(double* out) override {
     const Geo g = geo();
     launch_diag<R>(g, S.parts[cur], S.lay[lay], S.grids, S.dep[chi_last].chi, fp64_rows ? 1 : 0, S.diag_scratch,
-                   S.diag_out, stream);
+                   S.diag_out, S.err, stream);
     int rc = launched("diagnostics");
     if (rc) return rc;
-    if ((rc = hip_check(hipMemcpyAsync(out, S.diag_out, ENVPIC_NDIAG * sizeof(double), hipMemcpyDeviceToHost, stream), "diag read"))) return rc;
+    double h[ENVPIC_NDIAG + 1];  // the sums and the error word in one copy
+    if ((rc = hip_check(hipMemcpyAsync(h, S.diag_out, sizeof h, hipMemcpyDeviceToHost, stream), "diag read"))) return rc;
     if ((rc = hip_check(hipStreamSynchronize(stream), "diag sync"))) return rc;
-    return check_err();
+    std::memcpy(out, h, ENVPIC_NDIAG * sizeof(double));
+    return err_code((int)h[ENVPIC_NDIAG]);
   }
 
   // the same kernels with the partial sums in the library's static scratch
@@ -1115,7 +1123,7 @@ template <class R> struct SimT : envpic_sim {
     if ((size_t)diag_scratch_doubles() > diag_static_doubles)
       return fail(ENVPIC_EINVAL, "diagnostics partial sums exceed the static scratch");
     launch_diag<R>(geo(), S.parts[cur], S.lay[lay], S.grids, S.dep[chi_last].chi, fp64_rows ? 1 : 0, diag_static,
-                   dev_out, stream);
+                   dev_out, nullptr, stream);
     return launched("diagnostics (static scratch)");
   }
 
@@ -1128,13 +1136,16 @@ template <class R> struct SimT : envpic_sim {
     // fixed-point histogram: a power of two with capacity * w_max * scale <= 2^61
     const double wb = std::max(wmax, 1e-300) * (double)sz.capacity;
     a.scale = std::ldexp(1.0, std::min(1000, (int)std::floor(std::log2(std::ldexp(1.0, 61) / wb))));
-    launch_beam<R>(geo(), S.parts[cur], S.lay[lay], sz.max_items, a, S.beam, stream);
+    launch_beam<R>(geo(), S.parts[cur], S.lay[lay], sz.max_items, S.err, a, S.beam, stream);
     int rc = launched("beam diagnostics");
     if (rc) return rc;
-    if ((rc = hip_check(hipMemcpyAsync(out, S.beam.out, ENVPIC_NBEAM * sizeof(double), hipMemcpyDeviceToHost, stream), "beam read"))) return rc;
-    if (hist && (rc = hip_check(hipMemcpyAsync(hist, S.beam.hist_f, nbins * sizeof(double), hipMemcpyDeviceToHost, stream), "beam hist"))) return rc;
+    double h[ENVPIC_NBEAM + 1 + BEAM_MAX_BINS];  // the outputs, the error word and the histogram in one copy
+    const size_t nd = ENVPIC_NBEAM + 1 + (hist ? nbins : 0);
+    if ((rc = hip_check(hipMemcpyAsync(h, S.beam.out, nd * sizeof(double), hipMemcpyDeviceToHost, stream), "beam read"))) return rc;
     if ((rc = hip_check(hipStreamSynchronize(stream), "beam sync"))) return rc;
-    return check_err();
+    std::memcpy(out, h, ENVPIC_NBEAM * sizeof(double));
+    if (hist) std::memcpy(hist, h + ENVPIC_NBEAM + 1, nbins * sizeof(double));
+    return err_code((int)h[ENVPIC_NBEAM]);
   }
 
   int bunch(uint32_t id_lo, uint32_t id_hi, double beta, double tol, int max_iter, int* iters,

@@ -121,9 +121,10 @@ int diag_scratch_doubles();
 // on `device` (a file-scope device array; resolved once per device); 0 on
 // success
 int static_scratch(int device, double** ptr, size_t* doubles);
+// err: null, or the error word to follow the ENVPIC_NDIAG sums in out
 template <class R>
 void launch_diag(const Geo& g, const Parts<R>& P, const Layout& L, const Grids<R>& f, const R* chi, int fp64_rows,
-                 double* scratch, double* out, hipStream_t st);
+                 double* scratch, double* out, const int* err, hipStream_t st);
 
 // injected-beam parameters (beam.hip)
 constexpr int BEAM_MAX_BINS = 4096;
@@ -140,13 +141,15 @@ enum {
 };
 struct BeamScratch {
   unsigned long long* hist;  // [BEAM_MAX_BINS] fixed-point charge per bin
-  double* hist_f;            // [BEAM_MAX_BINS] the same as FP64 (charge units)
   double* part;              // [max_items][BEAM_PARTS] per-item partial sums
   double* st;                // [BEAM_STATE]
-  double* out;               // [ENVPIC_NBEAM]
+  unsigned long long* bits;  // [max_items][item_words] a bit per particle of an item: in the spectrum's range
+  int item_words;
+  double* out;               // [ENVPIC_NBEAM], the error word, then hist_f
+  double* hist_f;            // [BEAM_MAX_BINS] the histogram as FP64 (charge units)
 };
 template <class R>
-void launch_beam(const Geo& g, const Parts<R>& P, const Layout& L, int max_items, const BeamArgs& a,
+void launch_beam(const Geo& g, const Parts<R>& P, const Layout& L, int max_items, const int* err, const BeamArgs& a,
                  const BeamScratch& b, hipStream_t st);
 
 // self-consistent fields of an injected bunch (bunch.hip): conjugate
