@@ -28,8 +28,44 @@ namespace envpic {
 __device__ inline double recip_r(double x) { return 1.0 / x; }
 __device__ inline float recip_r(float x) { return __builtin_amdgcn_rcpf(x); }
 
+// The kernel is short (4 to 8 us, half of it a chain of latencies), so the
+// constants of the scheme come as arguments: one wavefront per column holds
+// FP64 rows, and five FP64 divisions there made the longest chain, and the
+// column of a flat node index takes a multiplication instead of a division.
+template <class R> struct EnvConst {
+  double dt, pre_r, pre_i, idx1, idx2, idr2, ir1;
+  R rdt, rpre_r, rpre_i, ridx1, ridx2, ridr2;
+  unsigned magic;  // column of node idx: mulhi(idx, magic) >> shift, for idx < 2^31
+  int shift;
+};
+template <class R> EnvConst<R> env_const(const Geo& g) {
+  EnvConst<R> c{};
+  c.dt = g.dt;
+  c.pre_r = 1.0 / (1.0 + g.dt * g.dt);
+  c.pre_i = g.dt / (1.0 + g.dt * g.dt);
+  c.idx1 = 1.0 / g.dx;
+  c.idx2 = 1.0 / (g.dx * g.dx);
+  c.idr2 = 1.0 / (g.dr * g.dr);
+  c.ir1 = 1.0 / (2.0 * g.dr * g.dr);  // 1/(2 r_1 dr), r_1 = dr
+  c.rdt = (R)g.dt;
+  c.rpre_r = (R)c.pre_r;
+  c.rpre_i = (R)c.pre_i;
+  c.ridx1 = (R)c.idx1;
+  c.ridx2 = (R)c.idx2;
+  c.ridr2 = (R)c.idr2;
+  // floor(n / d) = floor(n M / 2^(31 + s)) for n < 2^31, 2^(s-1) < d <= 2^s,
+  // M = ceil(2^(31 + s) / d): the excess M d - 2^(31 + s) is below 2^s
+  const unsigned long long d = (unsigned long long)g.nr + 1;
+  int s = 1;
+  while ((1ull << s) < d) ++s;
+  c.magic = (unsigned)(((1ull << (31 + s)) + d - 1) / d);
+  c.shift = s - 1;
+  return c;
+}
+
 template <class R>
-__global__ void k_envelope(Geo g, Grids<R> f, const R* __restrict__ chi, int fp64_rows, SettleArgs<R> sa) {
+__global__ void k_envelope(Geo g, Grids<R> f, const R* __restrict__ chi, int fp64_rows, EnvConst<R> ec,
+                           SettleArgs<R> sa) {
   using C = typename cplx_of<R>::type;
   const int node_groups = (int)gridDim.x - sa.blocks;
   if ((int)blockIdx.x >= node_groups) {  // the copy back of a rebuilt tile sort
@@ -39,7 +75,7 @@ __global__ void k_envelope(Geo g, Grids<R> f, const R* __restrict__ chi, int fp6
   const int nr1 = g.nr + 1;
   const int idx = (int)(blockIdx.x * blockDim.x + threadIdx.x);  // nodes < 2^31
   if (idx >= (g.nx + 1) * nr1) return;
-  const int i = idx / nr1, j = idx - i * nr1;
+  const int i = (int)(__umulhi((unsigned)idx, ec.magic) >> ec.shift), j = idx - i * nr1;
   const int pc = phys_col(g, i);
   const size_t o = (size_t)pc * g.pitch + j;
   const bool rows64 = fp64_rows && j <= 1;
@@ -49,11 +85,10 @@ __global__ void k_envelope(Geo g, Grids<R> f, const R* __restrict__ chi, int fp6
     return;
   }
   const int pp = phys_col(g, i + 1), pm = phys_col(g, i - 1);
-  const double dt = g.dt;
-  const double pre_r = 1.0 / (1.0 + dt * dt), pre_i = dt / (1.0 + dt * dt);
   if (rows64) {
+    const double dt = ec.dt, pre_r = ec.pre_r, pre_i = ec.pre_i;
     const double2 a = f.ax[pc * 2 + j], aip = f.ax[pp * 2 + j], aim = f.ax[pm * 2 + j];
-    const double idx2 = 1.0 / (g.dx * g.dx), idr2 = 1.0 / (g.dr * g.dr);
+    const double idx2 = ec.idx2, idr2 = ec.idr2;
     double2 lap = make_double2((aip.x - 2.0 * a.x + aim.x) * idx2, (aip.y - 2.0 * a.y + aim.y) * idx2);
     if (j == 0) {
       const double2 up = f.ax[pc * 2 + 1];
@@ -62,12 +97,12 @@ __global__ void k_envelope(Geo g, Grids<R> f, const R* __restrict__ chi, int fp6
     } else {
       const C u = f.env[o + 1];
       const double2 up = make_double2((double)u.x, (double)u.y), dn = f.ax[pc * 2 + 0];
-      const double ir = 1.0 / (2.0 * g.dr * g.dr);  // 1/(2 r_1 dr), r_1 = dr
+      const double ir = ec.ir1;
       lap.x += (up.x - 2.0 * a.x + dn.x) * idr2 + (up.x - dn.x) * ir;
       lap.y += (up.y - 2.0 * a.y + dn.y) * idr2 + (up.y - dn.y) * ir;
     }
     const double ch = (double)chi[o];
-    const double i2dx = 1.0 / g.dx;  // 2i (d)/(2 dx) = i d / dx
+    const double i2dx = ec.idx1;  // 2i (d)/(2 dx) = i d / dx
     const double rr = lap.x - ch * a.x - (aip.y - aim.y) * i2dx;
     const double ri = lap.y - ch * a.y + (aip.x - aim.x) * i2dx;
     const double2 ap = f.axp[pc * 2 + j];
@@ -78,10 +113,9 @@ __global__ void k_envelope(Geo g, Grids<R> f, const R* __restrict__ chi, int fp6
     f.envp[o] = mk<C>((R)an.x, (R)an.y);
     return;
   }
-  const R rdt = (R)dt;
+  const R rdt = ec.rdt;
   const C a = f.env[o], aip = f.env[(size_t)pp * g.pitch + j], aim = f.env[(size_t)pm * g.pitch + j];
-  const R idx1 = recip_r((R)g.dx), idr1 = recip_r((R)g.dr);
-  const R idx2 = idx1 * idx1, idr2 = idr1 * idr1;
+  const R idx2 = ec.ridx2, idr2 = ec.ridr2;
   R lx = (aip.x - (R)2 * a.x + aim.x) * idx2, ly = (aip.y - (R)2 * a.y + aim.y) * idx2;
   const C up = f.env[o + 1];
   if (j == 0) {
@@ -94,13 +128,13 @@ __global__ void k_envelope(Geo g, Grids<R> f, const R* __restrict__ chi, int fp6
     ly += (up.y - (R)2 * a.y + dn.y) * idr2 + (up.y - dn.y) * ir;
   }
   const R ch = chi[o];
-  const R i2dx = idx1;
+  const R i2dx = ec.ridx1;
   const R rr = lx - ch * a.x - (aip.y - aim.y) * i2dx;
   const R ri = ly - ch * a.y + (aip.x - aim.x) * i2dx;
   const C ap = f.envp[o];
   const R br = (R)2 * a.x - (ap.x - rdt * ap.y) + rdt * rdt * rr;
   const R bi = (R)2 * a.y - (ap.y + rdt * ap.x) + rdt * rdt * ri;
-  const R pr = recip_r((R)1 + rdt * rdt), pim = rdt * pr;
+  const R pr = ec.rpre_r, pim = ec.rpre_i;
   f.envp[o] = mk<C>(pr * br - pim * bi, pr * bi + pim * br);
 }
 
@@ -456,7 +490,7 @@ static inline int node_blocks(const Geo& g) {
 template <class R>
 void launch_envelope(const Geo& g, const Grids<R>& f, const R* chi, int fp64_rows, const SettleArgs<R>& sa,
                      hipStream_t st, const KEvents& ev) {
-  launch_k(k_envelope<R>, dim3(node_blocks(g) + sa.blocks), dim3(256), st, ev, g, f, chi, fp64_rows, sa);
+  launch_k(k_envelope<R>, dim3(node_blocks(g) + sa.blocks), dim3(256), st, ev, g, f, chi, fp64_rows, env_const<R>(g), sa);
 }
 
 template <class R>
