@@ -593,12 +593,34 @@ __global__ __launch_bounds__(WG, (mom_waves_per_simd<R, M1, DEFER, SCAT, O>())) 
   // the tile's overflow range riding with it
   const int total = it.z + it.w, ov_base = (it.w > 0 ? Ls.ovb[it.x] : 0) - it.z;
   auto slot_of = [&](int k) { return k + (k < it.z ? it.y : ov_base); };
-  // the cell word of the next particle is loaded one turn ahead: the rest of
+  // The cell word of the next particle is loaded one turn ahead: the rest of
   // the record follows it at once (the compiler places those loads behind
-  // the test for a removed particle); the first ones arrive while the region
-  // is staged
+  // the test for a removed particle).  In the FP32 in-place pass of large
+  // runs the rest is loaded at the end of the turn before (the first one while
+  // the region is staged): 86.4 us instead of 90.8 at 8.4 M particles, 1279
+  // instead of 1314 at 151 M.  Where the records are still in the last-level
+  // cache it gives nothing (29.8 and 30.1 at 2.2 M), and the others lose by it,
+  // to registers (FP64 in place 161 -> 174) or to what a sort does between the
+  // loads and their use (102.5 -> 109).
+  constexpr bool AHEAD = SCAT == SCAT_NONE && sizeof(R) == 4 && NT;
+  struct Rec {
+    R fx, fr, th, w, p[3];
+  };
+  auto fetch = [&](int p) {
+    Rec v;
+    v.fx = pld<NT>(elem(src.fx, p));
+    v.fr = pld<NT>(elem(src.fr, p));
+    v.th = pld<NT>(elem(src.th, p));
+    v.w = pld<NT>(elem(src.w, p));
+    v.p[0] = pld<NT>(elem(src.px, p));
+    v.p[1] = pld<NT>(elem(src.py, p));
+    v.p[2] = pld<NT>(elem(src.pz, p));
+    return v;
+  };
   unsigned cw_next = kDead;
   if (threadIdx.x < total) cw_next = pld<NT>(elem(src.cell, slot_of(threadIdx.x)));
+  Rec rec{};
+  if (AHEAD && threadIdx.x < total) rec = fetch(slot_of(threadIdx.x));
 
   // ---- stage E, Bbar, Phi (and mode 1) of the region in LDS.  Every load
   // reads a valid address (the index falls back to the column start) and the
@@ -850,7 +872,21 @@ __global__ __launch_bounds__(WG, (mom_waves_per_simd<R, M1, DEFER, SCAT, O>())) 
   const int seg_end = SCAT == SCAT_TILE ? Ls.offsets[g.ntiles] : 0;
 
   // ---- gather, push, deposit, scatter
-  {
+  if constexpr (AHEAD) {
+    for (int k = threadIdx.x; k < total; k += WG) {
+      const unsigned cw = cw_next;
+      const int p = slot_of(k), pn = slot_of(k + WG);
+      const bool more = k + WG < total;
+      if (more) cw_next = pld<NT>(elem(src.cell, pn));
+      if (cw != kDead) {
+        push(cw, rec.fx, rec.fr, rec.th, rec.w, rec.p, p);
+        pst<NT>(elem(src.px, p), rec.p[0]);
+        pst<NT>(elem(src.py, p), rec.p[1]);
+        pst<NT>(elem(src.pz, p), rec.p[2]);
+      }
+      if (more) rec = fetch(pn);
+    }
+  } else {
     // (SCAT_TILE ranks over whole wavefronts: uniform trip count)
     const int trips = SCAT == SCAT_TILE ? (total + 63) & ~63 : total;
     for (int k = threadIdx.x; k < trips; k += WG) {
