@@ -32,6 +32,7 @@ __device__ inline float recip_r(float x) { return __builtin_amdgcn_rcpf(x); }
 // constants of the scheme come as arguments: one wavefront per column holds
 // FP64 rows, and five FP64 divisions there made the longest chain, and the
 // column of a flat node index takes a multiplication instead of a division.
+// 4.3 -> 4.0 us at 256 x 32, 8.2 -> 7.7 at 2048 x 256 (15 MB: 2.5 us).
 template <class R> struct EnvConst {
   double dt, pre_r, pre_i, idx1, idx2, idr2, ir1;
   R rdt, rpre_r, rpre_i, ridx1, ridx2, ridr2;
