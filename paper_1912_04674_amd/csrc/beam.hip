@@ -23,8 +23,8 @@
 // leaves a bit per particle that lies in the range; peak (one work group); and
 // for each moment pass a kernel per item, which reads only the particles
 // whose bit is set, and a one-group fixed-order reduction.  The range is
-// meant to hold a beam out of a plasma, so the moment passes are short (20 and
-// 16 us where 1.4 % of 8.4 M particles are in range, latency; 48 and 47 when
+// meant to hold a beam out of a plasma, so the moment passes are short (18 and
+// 14 us where 1.4 % of 8.4 M particles are in range, latency; 48 and 47 when
 // they read every record), and the histogram, bound by its 168 MB (28 us at
 // the rate of a large copy), takes 29 to 31 us (43 before its loads were
 // issued turns ahead).
@@ -44,6 +44,11 @@ namespace envpic {
 
 constexpr int BG = 256;      // threads of the histogram kernel's groups
 constexpr int BM = 512;      // threads of the moment kernels' groups
+// Their groups: as many as the device holds at once, each taking every
+// MOMENT_GROUPS-th item.  Most items hold no particle in range, and a group
+// per item the layout may have costs 2 ns each to dispatch: 18 and 14 us instead
+// of 21 and 16 (and 21 and 18 with 512 groups of 1024 threads).
+constexpr int MOMENT_GROUPS = 1024;
 constexpr int BPK = 1024;    // threads of the peak kernel
 constexpr int NBM = BEAM_PARTS;  // partial sums per item in each moment pass
 
@@ -208,72 +213,74 @@ __global__ __launch_bounds__(BPK) void k_beam_peak(BeamArgs a, BeamScratch b) {
 template <class R, int PASS>
 __global__ __launch_bounds__(BM) void k_beam_moments(Geo g, Parts<R> P, Layout L, BeamArgs a, BeamScratch b) {
   __shared__ double red[BM / 64][NBM];
-  double v[NBM] = {0, 0, 0, 0, 0, 0, 0, 0};
-  const int item = blockIdx.x;
-  if (item >= *L.n_items) return;
+  const int n_items = *L.n_items;
   const double lo = b.st[BS_LO], hi = b.st[BS_HI];
   const double em = b.st[BS_EMEAN], ym = b.st[BS_YMEAN], zm = b.st[BS_ZMEAN];
   const double pym = b.st[BS_PYMEAN], pzm = b.st[BS_PZMEAN];
-  const int4 it = L.items[item];
-  const int words = (it.z + it.w + 63) >> 6;
-  const unsigned long long* bits = b.bits + (size_t)item * b.item_words;
-  // wavefront q takes every (BM / 64)-th word from q on; a lane holds one of them, and
-  // the wavefront goes through those that are not zero
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  bool any = false;
-  for (int w0 = wave; w0 < words; w0 += 64 * (BM / 64)) {
-    const int mine = w0 + lane * (BM / 64);
-    const unsigned long long held = mine < words ? bits[mine] : 0ull;
-    for (unsigned long long some = __ballot(held != 0ull); some; some &= some - 1) {
-      any = true;
-      const int from = __ffsll(some) - 1;
-      const unsigned long long word = __shfl(held, from, 64);
-      if ((word >> lane) & 1ull) {
-        const int p = item_slot(L, it, (w0 + from * (BM / 64)) * 64 + lane);
-        const unsigned cw = P.cell[p];
-        const double px = P.px[p], py = P.py[p], pz = P.pz[p];
-        const double e = kin_energy(px, py, pz);
-        const double w = P.w[p];
-        if (PASS == 1) v[7] += w;
-        if (!(e >= lo && e <= hi)) continue;
-        const double r = ((double)cell_jr(cw) + (double)P.fr[p]) * g.dr;
-        double sn, cs;
-        sincos_r((double)P.th[p], &sn, &cs);
-        const double y = r * cs, z = r * sn;
-        if (PASS == 1) {
-          v[0] += w;
-          v[1] += w * e;
-          v[2] += w * y;
-          v[3] += w * z;
-          v[4] += w * py;
-          v[5] += w * pz;
-          v[6] += 1.0;
-        } else {
-          const double de = e - em, dy = y - ym, dz = z - zm, dpy = py - pym, dpz = pz - pzm;
-          v[0] += w * de * de;
-          v[1] += w * dy * dy;
-          v[2] += w * dpy * dpy;
-          v[3] += w * dy * dpy;
-          v[4] += w * dz * dz;
-          v[5] += w * dpz * dpz;
-          v[6] += w * dz * dpz;
+  for (int item = blockIdx.x; item < n_items; item += gridDim.x) {
+    double v[NBM] = {0, 0, 0, 0, 0, 0, 0, 0};
+    const int4 it = L.items[item];
+    const int words = (it.z + it.w + 63) >> 6;
+    const unsigned long long* bits = b.bits + (size_t)item * b.item_words;
+    // wavefront q takes every (BM / 64)-th word from q on; a lane holds one of
+    // them, and the wavefront goes through those that are not zero
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    bool any = false;
+    for (int w0 = wave; w0 < words; w0 += 64 * (BM / 64)) {
+      const int mine = w0 + lane * (BM / 64);
+      const unsigned long long held = mine < words ? bits[mine] : 0ull;
+      for (unsigned long long some = __ballot(held != 0ull); some; some &= some - 1) {
+        any = true;
+        const int from = __ffsll(some) - 1;
+        const unsigned long long word = __shfl(held, from, 64);
+        if ((word >> lane) & 1ull) {
+          const int p = item_slot(L, it, (w0 + from * (BM / 64)) * 64 + lane);
+          const unsigned cw = P.cell[p];
+          const double px = P.px[p], py = P.py[p], pz = P.pz[p];
+          const double e = kin_energy(px, py, pz);
+          const double w = P.w[p];
+          if (PASS == 1) v[7] += w;
+          if (!(e >= lo && e <= hi)) continue;
+          const double r = ((double)cell_jr(cw) + (double)P.fr[p]) * g.dr;
+          double sn, cs;
+          sincos_r((double)P.th[p], &sn, &cs);
+          const double y = r * cs, z = r * sn;
+          if (PASS == 1) {
+            v[0] += w;
+            v[1] += w * e;
+            v[2] += w * y;
+            v[3] += w * z;
+            v[4] += w * py;
+            v[5] += w * pz;
+            v[6] += 1.0;
+          } else {
+            const double de = e - em, dy = y - ym, dz = z - zm, dpy = py - pym, dpz = pz - pzm;
+            v[0] += w * de * de;
+            v[1] += w * dy * dy;
+            v[2] += w * dpy * dpy;
+            v[3] += w * dy * dpy;
+            v[4] += w * dz * dz;
+            v[5] += w * dpz * dpz;
+            v[6] += w * dz * dpz;
+          }
         }
       }
     }
-  }
-  // sums over the lanes (fixed order), then over the wavefronts
-  if (any) {
+    // sums over the lanes (fixed order), then over the wavefronts
+    if (any) {
 #pragma unroll
-    for (int k = 0; k < NBM; ++k)
-      for (int o = 32; o >= 1; o >>= 1) v[k] += __shfl_xor(v[k], o, 64);
-  }
-  if (lane == 0)
-    for (int k = 0; k < NBM; ++k) red[wave][k] = v[k];
-  __syncthreads();
-  if (threadIdx.x < NBM) {
-    double t = 0.0;
-    for (int q = 0; q < BM / 64; ++q) t += red[q][threadIdx.x];
-    b.part[(size_t)item * NBM + threadIdx.x] = t;
+      for (int k = 0; k < NBM; ++k)
+        for (int o = 32; o >= 1; o >>= 1) v[k] += __shfl_xor(v[k], o, 64);
+    }
+    if (lane == 0)
+      for (int k = 0; k < NBM; ++k) red[wave][k] = v[k];
+    __syncthreads();
+    if (threadIdx.x < NBM) {
+      double t = 0.0;
+      for (int q = 0; q < BM / 64; ++q) t += red[q][threadIdx.x];
+      b.part[(size_t)item * NBM + threadIdx.x] = t;
+    }
+    __syncthreads();  // red is free again
   }
 }
 
@@ -341,12 +348,13 @@ template <class R>
 void launch_beam(const Geo& g, const Parts<R>& P, const Layout& L, int max_items, const int* err, const BeamArgs& a,
                  const BeamScratch& b, hipStream_t st) {
   const int nclr = (std::max(a.nbins, (int)BEAM_STATE) + BG - 1) / BG;
+  const int mg = std::min(max_items, MOMENT_GROUPS);
   hipLaunchKernelGGL(k_beam_clear, dim3(nclr), dim3(BG), 0, st, b, a.nbins);
   hipLaunchKernelGGL((k_beam_hist<R>), dim3(max_items), dim3(BG), a.nbins * sizeof(long long), st, P, L, a, b);
   hipLaunchKernelGGL(k_beam_peak, dim3(1), dim3(BPK), 0, st, a, b);
-  hipLaunchKernelGGL((k_beam_moments<R, 1>), dim3(max_items), dim3(BM), 0, st, g, P, L, a, b);
+  hipLaunchKernelGGL((k_beam_moments<R, 1>), dim3(mg), dim3(BM), 0, st, g, P, L, a, b);
   hipLaunchKernelGGL(k_beam_reduce<1>, dim3(1), dim3(BR * NBM), 0, st, L, err, a, b);
-  hipLaunchKernelGGL((k_beam_moments<R, 2>), dim3(max_items), dim3(BM), 0, st, g, P, L, a, b);
+  hipLaunchKernelGGL((k_beam_moments<R, 2>), dim3(mg), dim3(BM), 0, st, g, P, L, a, b);
   hipLaunchKernelGGL(k_beam_reduce<2>, dim3(1), dim3(BR * NBM), 0, st, L, err, a, b);
 }
 

@@ -61,7 +61,8 @@ constexpr int WG = 512;     // work-group size of the particle kernels
 constexpr int CHUNK = 4096; // largest work item (particles); small runs use smaller items
 // A tile's overflow range of at most this many particles rides with the
 // tile's last work item instead of making one of its own, which would stage
-// the tile's region and flush its deposits once more.  (The fixed-point
+// the tile's region and flush its deposits once more (1024 x 128 cells, with the
+// tickets of the tile sort: 1246 -> 1213 us for 24 steps).  (The fixed-point
 // sums hold items of CHUNK + MAX_RIDERS particles.)
 constexpr int MAX_RIDERS = 1024;
 // Tile segments and their work items start at multiples of SLOT_ALIGN slots, a

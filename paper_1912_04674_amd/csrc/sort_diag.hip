@@ -61,12 +61,12 @@ __device__ inline void group_sum(const double (&v)[N], double* out) {
 // of the groups a third full at 8.4 M particles).  32 bytes a particle bound
 // it: the loads of DU turns are issued before any is used, since the 16
 // wavefronts of a CU do not cover them, and the sine and cosine are the short
-// series of the azimuth's range.  8.4 M particles: 49 us (67 before; 46 at
-// the rate of a large copy).
+// series of the azimuth's range.  8.4 M particles: 49 us alone (67 before; 46 at
+// the rate of a large copy), 55 to 58 with the grid sums beside it.
 constexpr int DQ = 4;  // parts of an item
 constexpr int DU = 2;
 template <class R>
-__global__ __launch_bounds__(DG) void k_diag_particles(Geo g, Parts<R> P, Layout L, double* __restrict__ part) {
+__device__ inline void diag_particles(const Geo& g, const Parts<R>& P, const Layout& L, double* __restrict__ part) {
   double v[NPD] = {0, 0, 0, 0, 0, 0};
   const int n_units = *L.n_items * DQ;
   for (int unit = blockIdx.x; unit < n_units; unit += DIAG_BLOCKS) {
@@ -117,14 +117,14 @@ __global__ __launch_bounds__(DG) void k_diag_particles(Geo g, Parts<R> P, Layout
 // per group: sum chi V, sum |A|^2 V, mode-0 and mode-1 field energy sums,
 // non-finite count over the nodes idx = (b + k DIAG_BLOCKS) DG + t
 template <class R>
-__global__ __launch_bounds__(DG) void k_diag_grid(Geo g, Grids<R> f, const R* __restrict__ chi, int fp64_rows,
-                                                  double* __restrict__ part) {
+__device__ inline void diag_grid(const Geo& g, const Grids<R>& f, const R* __restrict__ chi, int fp64_rows, int blk,
+                                 double* __restrict__ part) {
   using C = typename cplx_of<R>::type;
   double v[NGD] = {0, 0, 0, 0, 0};
   const int nr1 = g.nr + 1;
   const long long nodes = (long long)(g.nx + 1) * nr1;
   const double pi = 3.14159265358979323846;
-  for (long long idx = (long long)blockIdx.x * DG + threadIdx.x; idx < nodes; idx += (long long)DIAG_BLOCKS * DG) {
+  for (long long idx = (long long)blk * DG + threadIdx.x; idx < nodes; idx += (long long)DIAG_BLOCKS * DG) {
     const int i = (int)(idx / nr1), j = (int)(idx - (long long)i * nr1);
     const int pc = phys_col(g, i);
     const size_t o = (size_t)pc * g.pitch + j;
@@ -158,7 +158,19 @@ __global__ __launch_bounds__(DG) void k_diag_grid(Geo g, Grids<R> f, const R* __
       if (i <= g.nx - 1 && j <= g.nr - 1) v[3] += (double)cnorm(bt1) * vh;
     }
   }
-  group_sum<NGD>(v, part + (size_t)blockIdx.x * NGD);
+  group_sum<NGD>(v, part + (size_t)blk * NGD);
+}
+
+// the particle sums by the first DIAG_BLOCKS groups, the grid sums by the
+// others, which fill the device as the first ones end (in a launch of its own
+// the grid part took another 12 us at 2048 x 256)
+template <class R>
+__global__ __launch_bounds__(DG) void k_diag_sums(Geo g, Parts<R> P, Layout L, Grids<R> f, const R* __restrict__ chi,
+                                                  int fp64_rows, double* __restrict__ pp, double* __restrict__ pg) {
+  if (blockIdx.x < DIAG_BLOCKS)
+    diag_particles<R>(g, P, L, pp);
+  else
+    diag_grid<R>(g, f, chi, fp64_rows, blockIdx.x - DIAG_BLOCKS, pg);
 }
 
 // the groups' sums in a fixed order (wavefront q sums quantity q), mapped
@@ -233,8 +245,7 @@ void launch_diag(const Geo& g, const Parts<R>& P, const Layout& L, const Grids<R
                  double* scratch, double* out, const int* err, hipStream_t st) {
   double* pp = scratch;
   double* pg = scratch + (size_t)DIAG_BLOCKS * NPD;
-  hipLaunchKernelGGL((k_diag_particles<R>), dim3(DIAG_BLOCKS), dim3(DG), 0, st, g, P, L, pp);
-  hipLaunchKernelGGL((k_diag_grid<R>), dim3(DIAG_BLOCKS), dim3(DG), 0, st, g, f, chi, fp64_rows, pg);
+  hipLaunchKernelGGL((k_diag_sums<R>), dim3(2 * DIAG_BLOCKS), dim3(DG), 0, st, g, P, L, f, chi, fp64_rows, pp, pg);
   hipLaunchKernelGGL(k_diag_final, dim3(1), dim3(64 * (NPD + NGD)), 0, st, pp, pg, out, err);
 }
 
