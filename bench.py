@@ -249,7 +249,8 @@ def bunch_solve_line(workload):
     """The field initialisation of an injected bunch (gamma = 7.09) on the
     workload's grid: conjugate-gradient iterations, wall time of the
     synchronous call, and the algorithmic bytes of the iterations (per
-    unknown and iteration: stencil 16 B, update 48 B, direction 24 B)."""
+    unknown and iteration: preconditioner 36 B, direction 20 B, stencil 16 B,
+    update 48 B)."""
     import numpy as np
     import torch
     import paper_1912_04674_amd as E
@@ -271,7 +272,7 @@ def bunch_solve_line(workload):
     n = (cfg["nx"] - 1) * cfg["nr"]
     return {"workload": cfg["name"], "unknowns": n, "bunch_particles": nb, "beta": beta, "iterations": it,
             "relative_residual": res, "ms": 1e3 * dt, "us_per_iteration": 1e6 * dt / max(it, 1),
-            "alg_GBps": 88.0 * n * it / dt / 1e9}
+            "alg_GBps": 120.0 * n * it / dt / 1e9}
 
 
 def progress(*a):
@@ -400,10 +401,11 @@ def main():
              "gpu_event_ms_per_step": r32["gpu_ms"] / args.steps,
              "stage_avg_ms": r32["stage_ms"],
              "particles_start_end": [r32["n0"], r32["n1"]]}
-    # the beam pass reads cell, momentum and weight of every particle three
-    # times (histogram, means, centred moments): 60 B per particle
+    # the histogram reads cell, momentum and weight of every particle (20 B),
+    # the two moment passes these and the radial offset and azimuth (28 B) of
+    # the selected particles
     bm = r32["beam"]
-    bm["alg_bytes"] = 3 * (4 + 3 * 4 + 4) * r32["n1"]
+    bm["alg_bytes"] = (4 + 3 * 4 + 4) * r32["n1"] + 2 * 28 * int(bm["count"])
     bm["GBps_alg_incl_host_sync"] = bm["alg_bytes"] / (bm["ms"] * 1e-3) / 1e9
     extra["beam_diag"] = bm
     if args.workload == "c3" and cfg.get("sort_every") == 1:
