@@ -1,11 +1,12 @@
 """The bunch field solve over the grids where its sine-mode preconditioner can
 go wrong (edges of its 64-column, 32-row tiles and of the radial sweeps, the
-smallest grid, one radial row more than a sweep's threads) and the widest
-grids, which keep the diagonal, against the oracle's direct solve.
+smallest and the longest radial system, one row more than a sweep's
+threads) and the widest grids, which keep the diagonal, against the oracle's
+direct solve.
 
 Bars: |phi error| <= cond(K) * residual, and the fields are differences of phi
 over a cell.  The residual is 1e-13 and cond(K) at most 3e4 (the systems
-scaled to a unit diagonal; the longest row, 300 nodes, has the largest), so
+scaled to a unit diagonal; 193 x 300 has the largest), so
 1e-8 of each field's maximum.
 """
 import numpy as np
@@ -20,7 +21,8 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("nx,nr,beta,w", [
     (4, 2, 0.9, 1.0), (5, 33, 0.0, 1.0), (17, 31, 0.99, 1.0), (65, 32, 0.99, 1.0), (66, 34, 0.999, 1e-30),
-    (97, 65, 0.9, 1e30), (193, 300, 0.9, 1.0), (16384, 3, 0.9, 1.0), (16400, 4, 0.9, 1.0)])
+    (97, 65, 0.9, 1e30), (193, 300, 0.9, 1.0), (40, 513, 0.99, 1.0), (6, 1025, 0.9, 1.0), (5, 4094, 0.9, 1.0),
+    (16384, 3, 0.9, 1.0), (16400, 4, 0.9, 1.0)])
 def test_bunch_solve_grids(E, bunch_mod, nx, nr, beta, w):  # noqa: F811
     cfg = dict(nx=nx, nr=nr, dx=0.8, dr=1.5, dt=0.6, n_modes=1, profile="none", a0=0.0, ppc=(1, 1, 1),
                shape_order=1, capacity=2 * nx * nr + 4000)
