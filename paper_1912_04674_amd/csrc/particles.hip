@@ -19,6 +19,7 @@
 // displacement without cancellation, so the offsets keep their resolution at
 // any radius.
 #include <algorithm>
+#include <limits>
 
 #include "common.hpp"
 #include "cplx.hpp"
@@ -1039,6 +1040,10 @@ template <class R, bool M1> struct SmemPos {
   int tcnt[11];    // per-tile counts of the work item (flush_tiles)
 };
 
+// The largest value of the type below 2: an offset in [0, 1) after a step of
+// less than a cell (dt < dr; the stability limit accepts up to 0.97 dr)
+template <class R> constexpr R BELOW_TWO = (R)2 - std::numeric_limits<R>::epsilon();
+
 // one particle's move: old and new cells/offsets, transverse displacement
 // (radial a, azimuthal b, lengths) at the old azimuth, new azimuth, velocity
 template <class R> struct Move {
@@ -1081,8 +1086,8 @@ __device__ inline void push_position(const Geo& g, unsigned cw, R fx, R fr, R th
   const R r = ((R)mv.jr0 + fr) * dr;
   R drad, dth;
   mv.small = radial_step(r, mv.a, mv.b, drad, dth);
-  // (the radius stays >= 0 whatever the rounding)
-  const R r1 = clamp_r(fma(drad, pick<R>(g.rdr, g.rdr_f), fr), max((R)-1, -(R)mv.jr0), (R)1.875);
+  // (the radius stays >= 0 and the step below two cells whatever the rounding)
+  const R r1 = clamp_r(fma(drad, pick<R>(g.rdr, g.rdr_f), fr), max((R)-1, -(R)mv.jr0), BELOW_TWO<R>);
   mv.djr = floor_int(r1);
   mv.jr1 = mv.jr0 + mv.djr;
   mv.fr1 = fract_r(r1);
@@ -1139,7 +1144,7 @@ __device__ inline void mid_point(const Geo& g, const Move<R>& mv, int& djm, R& f
     c = rm > (R)0 ? ym / rm : (R)1;
     s = rm > (R)0 ? zm / rm : (R)0;
   }
-  f = clamp_r(f, max((R)-1, -(R)mv.jr0), (R)1.875);
+  f = clamp_r(f, max((R)-1, -(R)mv.jr0), BELOW_TWO<R>);
   djm = floor_int(f);
   frm = fract_r(f);
 }

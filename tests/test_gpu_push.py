@@ -54,7 +54,10 @@ def _particles(cfg, n, seed):
 def test_push_all_forms(E, oracle_mod, prec, tol, order):
     cfg = dict(nx=64, nr=24, dx=0.8, dr=1.5, dt=0.6, n_modes=2, profile="none", a0=0.0, ppc=(1, 1, 1),
                shape_order=order, capacity=60_000)
-    parts = _particles(cfg, 20_000, 5)
+    _push_and_compare(E, oracle_mod, cfg, _particles(cfg, 20_000, 5), prec, tol)
+
+
+def _push_and_compare(E, oracle_mod, cfg, parts, prec, tol):
     g = E.Sim(cfg, E.FP64 if prec == "fp64" else E.FP32_BULK)
     r = oracle_mod.OracleSim(cfg)
     g.set_particles(parts)
@@ -63,8 +66,8 @@ def test_push_all_forms(E, oracle_mod, prec, tol, order):
     r.step(1)
     a, b = by_id(g.get_particles()), by_id(r.get_particles())
     assert np.array_equal(a["id"], b["id"])
-    err = {k: float(np.abs(a[k] - b[k]).max() / s) for k, s in (("x", 0.8), ("y", 1.5), ("z", 1.5))}
-    say("push", prec, "order", order, err)
+    err = {k: float(np.abs(a[k] - b[k]).max() / cfg[s]) for k, s in (("x", "dx"), ("y", "dr"), ("z", "dr"))}
+    say("push", prec, "order", cfg["shape_order"], err)
     assert max(err.values()) <= tol
     # the currents follow the same move (mode 1 at its mid-point)
     for n in ("jx", "jr", "jx1", "jr1", "jt1"):
@@ -72,3 +75,29 @@ def test_push_all_forms(E, oracle_mod, prec, tol, order):
         e = float(np.abs(g.get_field(n) - ref).max() / np.abs(ref).max())
         say(n, f"{e:.1e}")
         assert e <= (1e-12 if prec == "fp64" else 2e-5), (n, e)
+
+
+# The largest moves that the stability limit accepts: with dx well above dr a
+# step crosses up to 0.965 dr, so a particle near the top of its cell ends up to
+# 1.965 cells above the cell's bottom.  Bars as above (the step is 0.96 cells).
+@pytest.mark.parametrize("order", [1, 2])
+@pytest.mark.parametrize("prec,tol", [("fp64", 1e-13), ("fp32", 1e-5)])
+@pytest.mark.parametrize("dx,dt", [(10.0, 0.96), (3.0, 0.91)])
+def test_push_near_the_step_limit(E, oracle_mod, dx, dt, prec, tol, order):
+    cfg = dict(nx=64, nr=24, dx=dx, dr=1.0, dt=dt, n_modes=2, profile="none", a0=0.0, ppc=(1, 1, 1),
+               shape_order=order, capacity=60_000)
+    parts = _particles(cfg, 20_000, 6)
+    rng = np.random.default_rng(7)
+    # half of them fast and radial, near the top of a cell or anywhere in it,
+    # outward (one in four inward)
+    k = np.arange(0, 20_000, 2)
+    n = k.size
+    fr = np.where(rng.uniform(size=n) < 0.5, 1 - 10.0 ** rng.uniform(-6, -1, n), rng.uniform(0, 1, n))
+    r = rng.integers(0, cfg["nr"], n) + np.minimum(fr, 0.999999)
+    th, p = rng.uniform(-np.pi, np.pi, n), 10.0 ** rng.uniform(0.5, 2, n) * rng.choice([1, 1, 1, -1], n)
+    slope = rng.normal(size=(2, n)) * 0.05
+    c, s = np.cos(th), np.sin(th)
+    for name, v in (("y", r * c), ("z", r * s), ("px", p * slope[0]), ("py", p * (c - s * slope[1])),
+                    ("pz", p * (s + c * slope[1]))):
+        parts[name][k] = v
+    _push_and_compare(E, oracle_mod, cfg, parts, prec, tol)
