@@ -101,3 +101,35 @@ def test_push_near_the_step_limit(E, oracle_mod, dx, dt, prec, tol, order):
                     ("pz", p * (s + c * slope[1]))):
         parts[name][k] = v
     _push_and_compare(E, oracle_mod, cfg, parts, prec, tol)
+
+
+def test_squares_beyond_fp64(E, oracle_mod):
+    """Momenta and magnetic fields that are accepted but whose squares are not
+    finite in FP64: 1/gamma and the rotation are zero, as in the oracle (equal
+    momenta; the particles at rest, the rest of the bars as above)."""
+    cfg = dict(nx=32, nr=16, dx=0.8, dr=1.5, dt=0.6, n_modes=2, profile="none", a0=0.0, ppc=(1, 1, 1))
+    parts = dict(x=np.array([8.0, 9, 10, 11]), y=np.array([3.0, 0, 5, 2]), z=np.array([1.0, 4, 0, 2]),
+                 px=np.array([1e160, 0.2, 1, 0.1]), py=np.array([0.0, -1e200, 1, 0.2]),
+                 pz=np.array([0.5, 1e158, 1, 0.3]), w=np.full(4, 1e-9), id=np.arange(4, dtype=np.uint32))
+    for field in (0.0, 1e160):
+        say("squares beyond fp64", field)
+        g = E.Sim(cfg, E.FP64)
+        r = oracle_mod.OracleSim(cfg)
+        g.set_particles(parts)
+        r.set_particles(parts)
+        bt = np.full((cfg["nx"] + 1, cfg["nr"] + 1), field)
+        g.set_field("bt_bar", bt)
+        r.set_field("bt_bar", bt)
+        g.gather_push(E.MOMENTUM)
+        r.momentum_chi()
+        a, b = by_id(g.get_particles()), by_id(r.get_particles())
+        for k in ("px", "py", "pz"):
+            np.testing.assert_allclose(a[k], b[k], rtol=1e-13, err_msg=k)
+        g.envelope_step()
+        r.envelope()
+        g.gather_push(E.POSITION)
+        r.position_J()
+        a, b = by_id(g.get_particles()), by_id(r.get_particles())
+        for k in ("x", "y", "z"):
+            np.testing.assert_allclose(a[k], b[k], rtol=1e-13, atol=1e-13, err_msg=k)
+        g.field_step()
