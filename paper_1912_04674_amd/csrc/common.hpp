@@ -264,6 +264,4 @@ __host__ __device__ inline double plasma_density(const Plasma& p, double xlab, l
   }
 }
 
-template <class T> __device__ inline T lds_get(const T* a, int x, int r) { return a[x * LR + r]; }
-
 }  // namespace envpic

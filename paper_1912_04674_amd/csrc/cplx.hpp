@@ -13,9 +13,6 @@ template <class C, class R> __host__ __device__ inline C mk(R re, R im) {
 template <class C> __host__ __device__ inline C cadd(C a, C b) { return mk<C>(a.x + b.x, a.y + b.y); }
 template <class C> __host__ __device__ inline C csub(C a, C b) { return mk<C>(a.x - b.x, a.y - b.y); }
 template <class C, class R> __host__ __device__ inline C cscale(C a, R s) { return mk<C>(a.x * s, a.y * s); }
-template <class C> __host__ __device__ inline C cmul(C a, C b) {
-  return mk<C>(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
-}
 // i * a
 template <class C> __host__ __device__ inline C cmuli(C a) { return mk<C>(-a.y, a.x); }
 template <class C> __host__ __device__ inline auto cnorm(C a) -> decltype(a.x) { return a.x * a.x + a.y * a.y; }

@@ -359,12 +359,6 @@ __device__ inline double dtheta(double b, double ra) {
   return copysign(x, b);
 }
 
-// carry an offset back into [0, 1): cell += floor(off), off -= floor(off)
-template <class R> __device__ inline void carry(int& cell, R& off) {
-  cell += floor_int(off);
-  off = fract_r(off);
-}
-
 // New radius and azimuth after a Cartesian transverse displacement with
 // radial component a and azimuthal component b (lengths) from radius r:
 // r' = |(r + a, b)|, written r' - r = a + (r + a)(sqrt(1 + beta^2) - 1) with
@@ -532,12 +526,6 @@ __device__ inline bool take_item(const Layout& L, int item, int4& it) {
   const int n = *L.n_items;
   asm volatile("" ::"s"(it.x), "s"(it.y), "s"(it.z), "s"(it.w));  // (keeps the load before the branch)
   return item < n;
-}
-
-// sum over the 64 lanes of a wavefront (every lane active)
-__device__ inline int wave_sum_i(int v) {
-  for (int m = 32; m >= 1; m >>= 1) v += __shfl_xor(v, m, 64);
-  return v;
 }
 
 // A ticket per lane from the global counter of its key (key < 0: none), with
