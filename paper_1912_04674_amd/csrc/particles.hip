@@ -173,8 +173,9 @@ __device__ inline void lds_add(double* a, double v) { atomicAdd(a, v); }
 // of the order in which the lanes land.  Each contribution is scaled by
 // g.fix = 2^32 / (2 w_max / V_0), the bound of any |2 q w v S / V| (|v| < 1,
 // S <= 1, V_0 the smallest node volume), so one contribution is at most 2^32
-// in magnitude and the <= 2 CHUNK contributions of a work item to one node
-// (and a fold of two such nodes) stay below 2^46.
+// in magnitude.  The particles of a work item and its riders add at most two
+// each to one node, below 2^45.4, and a fold of two such nodes stays below
+// 2^46.4.
 //
 // The float -> fixed conversion is one FP64 FMA: u x + 1.5 2^52 rounds u x
 // to the nearest integer v and its bit pattern is 0x4338 2^48 + v (exact for
@@ -210,6 +211,8 @@ __device__ inline double fixed_sum(long long w) {
   const int hi = (int)((((unsigned long long)w >> 32) & 0xFFFFu) ^ 0x8000u) | 0x43300000;
   return __hiloint2double(hi, (int)w) - 4644337115725824.0;  // 2^52 + 2^47
 }
+static_assert(4LL * (CHUNK + MAX_RIDERS) << 32 < 1LL << 47 && TR * 256 <= CHUNK + MAX_RIDERS,
+              "two contributions of 2^32 a particle, two nodes folded (an injected item: TR cells of at most 256)");
 __device__ inline bool fixed_nonzero(long long w) { return ((unsigned long long)w << 16) != 0; }
 template <> struct Acc1<float> {
   using T = longlong2;
@@ -231,9 +234,8 @@ template <> struct Acc1<float> {
 // inverse node volume or face area, which depend on the row only and are
 // applied once per node at the flush.  The FP64 path sums FP64 words; the
 // FP32 path sums fixed point as the mode-1 accumulators do, scaled by g.fix0
-// = 2^32 / w_max, so a contribution is at most 2^32 and the <= 2 CHUNK
-// contributions of a work item to one node (and a fold of two such nodes)
-// stay below 2^46 (exact, order-independent sums).
+// = 2^32 / w_max, so a contribution is at most 2^32 and the sums have the same
+// bound (exact, order-independent).
 template <class R> struct Acc0;
 template <> struct Acc0<double> {
   using T = double;
@@ -304,7 +306,8 @@ __device__ inline void sincos_r(float t, float* s, float* c) {
 // Series in b2 = beta^2 for |beta| < SMALL_BETA, the displacement of a step
 // against its radius: (sqrt(1 + b2) - 1) / b2, 1 / sqrt(1 + b2) and
 // atan(beta) / beta, to the rounding of the type (binomial and arctangent
-// series; the first omitted terms are below 6e-10 and 5e-17 of the sum).
+// series; the first omitted terms are at most 1.3e-9, 4.9e-9 and 2.2e-9 of the
+// sum in FP32 and 8e-18, 5.5e-17 and 1e-19 in FP64).
 // They replace a square root, a reciprocal square root and two reciprocals
 // per particle; only waves with a lane closer to the axis take the general
 // forms.

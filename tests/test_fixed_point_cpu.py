@@ -44,10 +44,11 @@ def test_bit_pattern_sums_equal_rounded_sums(seed):
     assert read_sum(word_sum(pats)) == int(exact.sum())
 
 
-def test_sum_at_the_bound_and_sign():
-    # 8192 contributions of +2^32 (and then of -2^32) reach 2^45 in magnitude,
-    # inside the +-2^47 the low 48 bits hold
-    n = 8192
+@pytest.mark.parametrize("n", [8192, 20480])
+def test_sum_at_the_bound_and_sign(n):
+    # 8192 contributions of +2^32 (and then of -2^32) reach 2^45 in magnitude;
+    # two of each of the 4096 + 1024 particles of the longest work item with its
+    # riders, on two nodes folded, 2^46.3: inside the +-2^47 the low 48 bits hold
     u = np.ones(n, np.float32)
     for sign in (1.0, -1.0):
         x = np.full(n, sign * 2.0**32, np.float32)
