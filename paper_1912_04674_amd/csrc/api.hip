@@ -546,7 +546,9 @@ template <class R> struct SimT : envpic_sim {
     g.shift = sh;
     g.cap = sz.capacity;
     g.base = (int)(sh % sz.nxa);
-    const long long c = sh - 2;
+    // a tile's place in the ring goes to the front once no particle of its work
+    // items can be alive: they are up to SORT_EVERY columns out of it
+    const long long c = sh - SORT_EVERY;
     g.t_lo = (int)(c >= 0 ? c / TX : -((-c + TX - 1) / TX));
     g.t_lo_ring = (g.t_lo % sz.ntxa + sz.ntxa) % sz.ntxa;
     g.dx = p.dx;

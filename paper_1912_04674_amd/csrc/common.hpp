@@ -117,7 +117,7 @@ struct Geo {
   int modes;
   int ppc_x, ppc_r, ppc_t;
   int base;          // shift mod nxa (physical column of the window's left edge)
-  int t_lo;          // lab tile index of column shift - 2
+  int t_lo;          // lab tile index of column shift - SORT_EVERY
   int t_lo_ring;     // its ring tile column, t_lo mod ntxa
   long long shift;   // lab column of the window's left edge
   long long cap;     // particle slots per buffer
