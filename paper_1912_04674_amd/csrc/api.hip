@@ -481,7 +481,12 @@ struct envpic_sim {
   // of steps, CELL_SORT_EVERY * SORT_EVERY, whatever the sort period: a cell
   // sort rewrites every particle (0.8 ms against 0.37 ms for a tile sort on
   // the 4096 x 512 workload sorting every step; every 24th sort by cell
-  // instead of every 8th took its pass of 8 steps from 6.83 to 6.45 ms).
+  // instead of every 8th took its pass of 8 steps from 6.83 to 6.45 ms).  The
+  // overflow ranges of a cycle's tile sorts add up, and late in a run one of 23
+  // finds no room and rebuilds the layout: sorting every step, steps 0 to
+  // 200 and 1000 to 1200 of the 2048 x 256 wakefield run take 230 and 287 us
+  // with every 24th, 238 and 272 with every 8th, 234 and 265 with every 12th;
+  // steps 500 to 600 of the 4096 x 512 workload 781, 839 and 811.
   // Quadratic shapes, whose passes feel the lost order more, keep every
   // CELL_SORT_EVERY-th sort.
   int cell_sort_period() const {
