@@ -112,3 +112,33 @@ def test_fields_come_back_as_set(E, prec, nx, nr):
         if name in dual_r:
             want[:, nr] = 0
         np.testing.assert_array_equal(g.get_field(name), want)
+
+
+def test_two_threads_read_one_simulation(E):
+    """Reads of one simulation from two threads at once: the particles are
+    ordered and the fields packed in scratch memory that the two share."""
+    import threading
+    cfg = dict(nx=256, nr=48, dx=0.8, dr=1.5, dt=0.6, n_modes=2, profile="uniform", n0=0.002, a0=1.0, w0=20.0,
+               tau=20.0, x_c=100.0, x_f=100.0, ppc=(2, 2, 2))
+    g = E.Sim(cfg, E.FP32_BULK)
+    g.step(4)
+    parts, fields = g.get_particles(), {n: g.get_field(n) for n in ("env", "ex", "bt1")}
+    blob = bytes(g.save())
+    wrong = []
+
+    def read(first):
+        for k in range(first, first + 12):
+            if k % 3 == 0:
+                got = g.get_particles()
+                wrong.extend(n for n in parts if not np.array_equal(got[n], parts[n]))
+            elif k % 3 == 1:
+                wrong.extend(n for n in fields if not np.array_equal(g.get_field(n), fields[n]))
+            elif bytes(g.save()) != blob:
+                wrong.append("save")
+
+    threads = [threading.Thread(target=read, args=(k,)) for k in range(2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not wrong, wrong

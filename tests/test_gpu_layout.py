@@ -91,3 +91,41 @@ def test_particles_at_the_left_edge_of_a_moving_window(E, oracle_mod, dx, dr, dt
             d = a[name][np.isin(a["id"], both)] - b[name][k][np.isin(b["id"][k], both)]
             assert np.abs(d).max() <= (1e-10 if prec == "fp64" else 2e-4) * size, name
     assert 1000 < len(both) < n
+
+
+@pytest.mark.parametrize("prec,tf,tp", PRECS)
+@pytest.mark.parametrize("small,base", [(True, 64), (True, 576), (False, 64), (False, 4160)])
+def test_riders_at_their_limit(E, oracle_mod, small, base, prec, tf, tp):
+    """A tile whose segment is full (a multiple of 64 particles, nearly at rest) gets,
+    in one tile sort, as many arrivals as ride with its last work item (256 with
+    items of 512 particles, 1024 with items of 4096), one fewer and one more,
+    three tiles away from each other; then the passes that go through them."""
+    limit = 256 if small else 1024
+    cfg = dict(nx=160 if small else 512, nr=32 if small else 128, dx=0.8, dr=1.5, dt=0.6, n_modes=2, profile="none",
+               a0=0.0, ppc=(1, 1, 1) if small else (8, 8, 4), capacity=20_000 if small else 17_400_000)
+    say("riders", prec, limit, base)
+    rng = np.random.default_rng(limit + base)
+    x, p = [], []
+    for tile, n in ((1, limit - 1), (4, limit), (7, limit + 1)):
+        edge = 16 * (tile + 1)
+        # 0.71 cells a step: one cell before the edge at the cell sort (step 3),
+        # one beyond it at the tile sort (step 6)
+        x += [edge - rng.uniform(3.2, 3.3, n), edge + rng.uniform(4, 12, base)]
+        p += [np.full(n, 3.0), np.zeros(base)]
+    x, p = np.concatenate(x), np.concatenate(p)
+    r, th = rng.uniform(1, 15, x.size) * cfg["dr"], rng.uniform(-np.pi, np.pi, x.size)
+    py, pz = rng.uniform(-0.05, 0.05, (2, x.size))
+    parts = dict(x=x * cfg["dx"], y=r * np.cos(th), z=r * np.sin(th), px=p, py=py, pz=pz,
+                 w=np.full(x.size, 1e-7), id=np.arange(x.size, dtype=np.uint32))
+    g = E.Sim(cfg, E.FP64 if prec == "fp64" else E.FP32_BULK)
+    o = oracle_mod.OracleSim(cfg)
+    g.set_particles(parts)
+    o.set_particles(parts)
+    for steps in (6, 1, 1, 2):  # (up to the sort, the sort, an in-place pass, another and the next sort)
+        g.step(steps)
+        o.step(steps)
+        assert g.state()[2] == x.size
+        compare_fields(g, o, tf, modes=2, names=("chi", "ex", "er", "bt", "bt_bar", "jx", "jr"))
+    compare_particles(g.get_particles(), o.get_particles(), tp, 1e-8 if prec == "fp64" else 1e-3)
+    stats = g.sort_stats()
+    assert stats["cell"] == 1 and stats["incremental"] >= 2 and stats["rebuilt"] == 0

@@ -408,19 +408,30 @@ def test_diagnostics_are_bitwise_reproducible(E):
         assert all(a[k] == b[k] for k in DIAG_KEYS), (a, b)
 
 
-@pytest.mark.parametrize("sort_every", [1, 2])
-def test_runtime_sort_period_parity(E, oracle_mod, sort_every):
+@pytest.mark.parametrize("prec,tf,tp", PRECS)
+@pytest.mark.parametrize("sort_every,order", [(1, 1), (2, 1), (1, 2)])
+def test_runtime_sort_period_parity(E, oracle_mod, sort_every, order, prec, tf, tp):
     """A particle sort every step (or every second step) instead of every
     third: the window run of modes 0 and 1 still matches the oracle, which
-    never sorts, after 100 steps (FP32 bars)."""
-    cfg = dict(C2_SMALL, sort_every=sort_every)
-    g = E.Sim(cfg, E.FP32_BULK)
-    r = oracle_mod.OracleSim(C2_SMALL)
+    never sorts, after 100 steps.  Cell sorts come every 24 steps with linear
+    shapes, every eighth sort with quadratic ones.  At the default capacity no
+    tile sort runs out of overflow room, but for those at the end of a cycle of
+    24 with a sort every step (the ranges add up over the cycle's tile sorts)."""
+    cfg = dict(C2_SMALL, sort_every=sort_every, shape_order=order)
+    g = E.Sim(cfg, _prec(E, prec))
+    r = oracle_mod.OracleSim(dict(C2_SMALL, shape_order=order))
     g.step(100)
     r.step(100)
     assert g.state() == r.state()
-    compare_fields(g, r, 1e-4, modes=2)
-    compare_particles(g.get_particles(), r.get_particles(), 1e-3, 1e-3)
+    compare_fields(g, r, tf, modes=2)
+    compare_particles(g.get_particles(), r.get_particles(), tp, 1e-8 if prec == "fp64" else 1e-3)
+    period = 8 if order == 2 else 24 // sort_every
+    done, scanned = 99 // sort_every, 100 // sort_every  # (the last scan is for step 101)
+    stats = g.sort_stats()
+    say("sort period", sort_every, "order", order, stats)
+    assert stats["cell"] == -(-done // period)
+    assert stats["incremental"] + stats["rebuilt"] == scanned - -(-scanned // period)
+    assert stats["rebuilt"] <= (100 // 24 if period == 24 else 0)
 
 
 @pytest.mark.parametrize("variant", [0, 1, 2, 3])
