@@ -403,7 +403,9 @@ def main():
              "particles_start_end": [r32["n0"], r32["n1"]]}
     # the histogram reads cell, momentum and weight of every particle (20 B),
     # the two moment passes these and the radial offset and azimuth (28 B) of
-    # the selected particles
+    # the particles in the window around the peak; a lower bound, as they also
+    # read the first 20 B of those elsewhere in the spectrum's range, whose
+    # number the call does not return
     bm = r32["beam"]
     bm["alg_bytes"] = (4 + 3 * 4 + 4) * r32["n1"] + 2 * 28 * int(bm["count"])
     bm["GBps_alg_incl_host_sync"] = bm["alg_bytes"] / (bm["ms"] * 1e-3) / 1e9
