@@ -173,10 +173,11 @@ typedef struct envpic_sim envpic_sim;
  * workloads C1..C5 (C4 gives its 2048 x 256 job shape). */
 void envpic_params_default(envpic_params* p, int preset);
 
-/* Validate `p` (sizes, one-cell-per-step CFL dt < dx, dt < dr, envelope and
- * Yee stability on this grid, finite floating-point fields, a non-negative
- * density and capacity) and report the arena bytes a simulation needs at
- * `precision`.  Returns ENVPIC_EINVAL with a message if invalid. */
+/* Validate `p` (sizes, one-cell-per-step CFL dt < dx, dt < dr, dt within 0.97
+ * of 1/sqrt(1/dx^2 + 1/dr^2), finite floating-point fields, a non-negative
+ * density and capacity; on cells with dx above 0.65 dr the Yee scheme needs dt
+ * below 2/sqrt(4.842/dr^2 + 4/dx^2), which is left to the caller) and report
+ * the arena bytes a simulation needs at `precision`.  Returns ENVPIC_EINVAL with a message if invalid. */
 int envpic_footprint(const envpic_params* p, int precision, size_t* bytes);
 
 /* Lay out and initialise a simulation inside `dev_arena` (device memory of
