@@ -175,9 +175,12 @@ void envpic_params_default(envpic_params* p, int preset);
 
 /* Validate `p` (sizes, one-cell-per-step CFL dt < dx, dt < dr, dt within 0.97
  * of 1/sqrt(1/dx^2 + 1/dr^2), finite floating-point fields, a non-negative
- * density and capacity; on cells with dx above 0.65 dr the Yee scheme needs dt
- * below 2/sqrt(4.842/dr^2 + 4/dx^2), which is left to the caller) and report
- * the arena bytes a simulation needs at `precision`.  Returns ENVPIC_EINVAL with a message if invalid. */
+ * density and capacity) and report the arena bytes a simulation needs at
+ * `precision`.  The bound on dt is necessary for stability; near the axis the
+ * Yee scheme needs dt below 2/sqrt(4.842/dr^2 + 4/dx^2) with mode 0 and below
+ * 0.94 (dr about twice dx) to 0.79 (dx far above dr) of
+ * 1/sqrt(1/dx^2 + 1/dr^2) with mode 1, which is left to the caller.  Returns
+ * ENVPIC_EINVAL with a message if invalid. */
 int envpic_footprint(const envpic_params* p, int precision, size_t* bytes);
 
 /* Lay out and initialise a simulation inside `dev_arena` (device memory of

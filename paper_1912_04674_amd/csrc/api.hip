@@ -114,13 +114,14 @@ int validate(const envpic_params* p) {
   if (!(p->dx > 0 && p->dr > 0 && p->dt > 0)) return fail(ENVPIC_EINVAL, "dx, dr, dt must be positive");
   if (!(p->dt < p->dx && p->dt < p->dr))
     return fail(ENVPIC_EINVAL, "dt must be below dx and dr (particles move at most one cell per step)");
-  // Stability: with the axis rows included both the envelope scheme and the
-  // cylindrical Yee scheme are about 2 % stricter than the Cartesian bound
-  // 1/sqrt(1/dx^2 + 1/dr^2) on cells with dr about twice dx, as the workloads
-  // have; 0.97 of that bound keeps a margin there.  On cells longer in x the
-  // axis weighs more: mode 0 is stable up to 2/sqrt(4.842/dr^2 + 4/dx^2), which
-  // is below the accepted bound from dx = 0.65 dr on (0.951 of the Cartesian
-  // bound at dx = dr, 0.909 for dx far above dr); there the caller keeps to it.
+  // Stability: the axis rows make both the envelope scheme and the cylindrical
+  // Yee scheme stricter than the Cartesian bound 1/sqrt(1/dx^2 + 1/dr^2), mode 0
+  // by 2 % on cells with dr about twice dx (2/sqrt(4.842/dr^2 + 4/dx^2)); 0.97 of
+  // that bound keeps a margin there.  It is necessary, not sufficient, where
+  // the axis weighs more: the oracle's fields stay bounded up to 0.971, 0.952,
+  // 0.925 and 0.910 of the bound at dx/dr = 0.65, 1, 2 and 10 with mode 0, and
+  // up to 0.978, 0.942, 0.879, 0.824 and 0.794 at 0.3, 0.53, 1, 2 and 10 with
+  // mode 1 (the workloads run at 0.85, the nonlinear one, dx/dr = 0.23, at 0.92).
   const double cart = 1.0 / std::sqrt(1.0 / (p->dx * p->dx) + 1.0 / (p->dr * p->dr));
   if (p->dt > 0.97 * cart) {
     char buf[160];
