@@ -45,3 +45,29 @@ def test_filter_at_tile_edges(E, oracle_mod, prec, nx, nr, passes):  # noqa: F81
         err = np.abs(g.get_field(name) - r.get_field(name)).max()
         say(name, f"{err:.2e}")
         assert err <= (4 * passes + 4) * eps * np.abs(f).max(), (name, err)
+
+
+def test_filtered_current_of_the_entering_column(E, oracle_mod):  # noqa: F811
+    """A window run past one turn of the ring of columns (96 here): the filtered
+    current of the column that just entered is zero, not what the ring held.
+    Bar: the FP64 path's."""
+    cfg = dict(nx=31, nr=19, dx=0.8, dr=1.5, dt=0.6, n_modes=2, ppc=(2, 2, 2), profile="uniform", n0=0.01, a0=2.0,
+               w0=10.0, tau=6.0, x_c=16.0, x_f=16.0, moving_window=1, filter_passes=3, seed=191204691)
+    g = E.Sim(cfg, E.FP64)
+    r = oracle_mod.OracleSim(cfg)
+    f = 1e-3 * np.ones((32, 20)) + 0j
+    f[0] = f[31] = 0
+    f[:, 19] = 0
+    for s in (g, r):
+        s.set_field("er1", f)
+        s.set_field("et1", -1j * f)
+    g.step(150)
+    r.step(150)
+    for _ in range(4):
+        say("entering column", g.state()[:2])
+        for name in ("jx", "jr", "jx1", "jr1", "jt1"):
+            ref = r.get_field(name)
+            err, size = float(np.abs(g.get_field(name) - ref).max()), float(np.abs(ref).max())
+            assert err <= 1e-9 * size, name
+        g.step(1)
+        r.step(1)
