@@ -351,12 +351,10 @@ __device__ inline void maxwell_tile(const Geo& g, const Grids<R>& f, const Depos
 // start at zero, and the new left edge (rel = 0) takes its boundary values
 // (zero envelope; E_r and mode-1 E_t there are zeroed by the Maxwell tile).
 // Runs in the field-stage kernel before the host swaps the E/B copies, so
-// E and B are written in their new (_n) copies.  din, the current that the
-// stage reads (the filtered copy of it with the binomial filter, which the host
-// reads back), holds the ring's last turn at the entering primal column.
+// E and B are written in their new (_n) copies.
 template <class R, bool M1>
-__device__ inline void window_row(const Geo& g, const Grids<R>& f, const DepositBufs<R>& din,
-                                  const DepositBufs<R>& d0, const DepositBufs<R>& d1, int fp64_rows, int j) {
+__device__ inline void window_row(const Geo& g, const Grids<R>& f, const DepositBufs<R>& d0,
+                                  const DepositBufs<R>& d1, int fp64_rows, int j) {
   using C = typename cplx_of<R>::type;
   if (j > g.nr) return;
   const C z = mk<C>((R)0, (R)0);
@@ -368,7 +366,6 @@ __device__ inline void window_row(const Geo& g, const Grids<R>& f, const Deposit
   f.er_n[on] = 0;
   d0.chi[on] = 0; d1.chi[on] = 0;
   d0.jr[on] = 0; d1.jr[on] = 0;
-  din.jr[on] = 0;
   // half-shifted-x grids at the entering column
   f.ex_n[od] = 0;
   f.bt_n[od] = 0;
@@ -386,7 +383,6 @@ __device__ inline void window_row(const Geo& g, const Grids<R>& f, const Deposit
   if (M1) {
     f.er1_n[on] = z; f.et1_n[on] = z; f.bx1_n[on] = z; f.bxb1[on] = z;
     d0.jr1[on] = z; d1.jr1[on] = z; d0.jt1[on] = z; d1.jt1[on] = z;
-    din.jr1[on] = z; din.jt1[on] = z;
     f.ex1_n[od] = z; f.br1_n[od] = z; f.bt1_n[od] = z; f.brb1[od] = z; f.btb1[od] = z;
     d0.jx1[od] = z; d1.jx1[od] = z;
   }
@@ -411,7 +407,7 @@ __global__ __launch_bounds__(MW_T) void k_field(Geo g, Grids<R> f, DepositBufs<R
   if (blk < fa.nb_mw) {
     maxwell_tile<R, M1>(g, f, din, dnext, (blk / fa.nbx_mw) * MW_TI, (blk % fa.nbx_mw) * MW_TJ, fa.shifting != 0, sm);
   } else if (blk < fa.nb_mw + fa.nb_win) {
-    window_row<R, M1>(fa.gn, f, din, d0, d1, fa.fp64_rows, (blk - fa.nb_mw) * MW_T + threadIdx.x);
+    window_row<R, M1>(fa.gn, f, d0, d1, fa.fp64_rows, (blk - fa.nb_mw) * MW_T + threadIdx.x);
   } else {
     const int t = 2 * (blk - fa.nb_mw - fa.nb_win) + threadIdx.x / (TX * TR);
     const int lt = threadIdx.x % (TX * TR);
@@ -643,6 +639,9 @@ __device__ void filter_component(const Geo& g, const V* __restrict__ src, V* __r
       sum = vfma(taps.w[m], row[m], sum);
     }
     dst[(size_t)phys_col(g, i) * g.pitch + jj] = vpick(sum, i <= imax && jj <= jmax ? (R)1 : (R)0);
+    // the column past the window, which holds the ring's last turn, reads as
+    // zero once a shift has made it the last one
+    if (i == g.nx) dst[(size_t)phys_col(g, i + 1) * g.pitch + jj] = vpick(sum, (R)0);
   }
 }
 
