@@ -639,10 +639,12 @@ __device__ void filter_component(const Geo& g, const V* __restrict__ src, V* __r
       sum = vfma(taps.w[m], row[m], sum);
     }
     dst[(size_t)phys_col(g, i) * g.pitch + jj] = vpick(sum, i <= imax && jj <= jmax ? (R)1 : (R)0);
-    // the column past the window, which holds the ring's last turn, reads as
-    // zero once a shift has made it the last one
-    if (i == g.nx) dst[(size_t)phys_col(g, i + 1) * g.pitch + jj] = vpick(sum, (R)0);
   }
+  // the column past the window, which holds the ring's last turn, reads as zero
+  // once a shift has made it the last one
+  const int jz = j0 + (int)threadIdx.x;
+  if (i0 <= g.nx && g.nx < i0 + FT && threadIdx.x < FT && jz <= g.nr)
+    dst[(size_t)phys_col(g, g.nx + 1) * g.pitch + jz] = V{};
 }
 
 // work group: tile blockIdx.x / ncomp, component blockIdx.x % ncomp
